@@ -213,6 +213,157 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
   if (EPI == kEpiSwiglu && !PART && __any(oor) && lane == 0 && p.status) atomicOr(p.status, kStatusRange);
 }
 
+// ---------------------------------------------------------------- few rows
+// C = A W^T on at most 16 rows: bound by the read of the weights, so the kernel
+// is a reader of W with matrix-core products.  One workgroup takes 16 weight rows
+// (SwiGLU: 16 gate rows and the 16 matching up rows) over the whole of K; its NW
+// waves take contiguous slices of K, load their A and W fragments straight into
+// registers (16 bytes per lane; no wave shares a fragment with another, so LDS
+// would only add a copy) U steps of 32 ahead, and the partial tiles are summed in
+// wave order through LDS.  Every output column then has NW waves of loads in
+// flight, without partial sums in memory or a second launch.
+// Measured, fp16 weights, against one wave per 16 columns through an LDS ring
+// (128 x 64 tiles for SwiGLU): 5 rows, 4096 x 4096 13.0 -> 10.2 us, 4096 x 12288
+// 30.6 -> 21.5 us (4.7 TB/s, launch included), 2560 x 9728 22.7 -> 16.6 us, SwiGLU
+// 24576 x 4096 53.5 -> 38.9 us (5.2 TB/s); 16 rows, SwiGLU 54.3 -> 45.2 us.  What
+// is left over the read is the A fragments, which every workgroup fetches from
+// its L2: 1 row takes 2-3 us less than 8.
+// PK = 2 (at most 8 rows): a 16-row A fragment would be half repeats, so one load
+// brings two steps of the 8 rows (lanes li 0-7 the even step, 8-15 the odd one)
+// and the odd step's product takes the fragment rotated by 8 rows; rows 8-15 of
+// the product are never stored.
+__device__ __forceinline__ u32x4 rotate_8_rows(u32x4 v) {  // lane li of each 16 takes lane (li + 8) % 16
+  u32x4 o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    o[i] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x128, 0xf, 0xf, false);  // row_ror:8
+  return o;
+}
+
+template <int NW, int U, int PK, int EPI, bool WBF16>
+__global__ __launch_bounds__(64 * NW) void gemm_rows(const GemmParams p) {
+  static_assert((PK == 1 || PK == 2) && U % PK == 0, "packed steps");
+  constexpr int NT = EPI == kEpiSwiglu ? 2 : 1;  // 16-row weight tiles
+  constexpr int RP = 16 / PK;                    // rows of A held per step
+  __shared__ f32x4 red[NW][NT][64];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, la = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int KT = p.K / 32, KP = (KT + 1) / 2;  // steps of 32; pairs of steps (whole 128-byte lines of W)
+  const int kb = 2 * (KP * wave / NW), ke = min(KT, 2 * (KP * (wave + 1) / NW));
+
+  // rows past M read row M - 1 again; never stored
+  const uint16_t* ap = (const uint16_t*)p.a + (int64_t)min(li % RP, p.M - 1) * p.lda + 8 * la;
+  const uint16_t* wp[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int n = 16 * blockIdx.x;  // a 16-column tile lies inside one block of weight rows
+    const int src = EPI == kEpiSwiglu ? j : n < p.b_split0 ? 0 : (n < p.b_split1 ? 1 : 2);
+    const int row = n - (EPI == kEpiSwiglu || src == 0 ? 0 : (src == 1 ? p.b_split0 : p.b_split1));
+    const void* b = src == 0 ? p.b[0] : (src == 1 ? p.b[1] : p.b[2]);
+    wp[j] = (const uint16_t*)b + (int64_t)(row + li) * p.ldb + 8 * la;
+  }
+
+  f32x4 acc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  struct Frag { u32x4 a[U / PK], w[U][NT]; };
+  Frag f0, f1;
+  auto load = [&](Frag& f, int k) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kk = 32 * min(k + u, ke - 1);  // steps past the slice re-read its last one, unused
+#pragma unroll
+      for (int j = 0; j < NT; ++j) f.w[u][j] = ld16v(wp[j] + kk);
+    }
+#pragma unroll
+    for (int u = 0; u < U / PK; ++u) f.a[u] = ld16v(ap + 32 * min(k + PK * u + li / RP, ke - 1));
+  };
+  auto mul = [&](const Frag& f, int k) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k + u >= ke) break;
+      const f16x8 a = __builtin_bit_cast(f16x8, u % PK == 0 ? f.a[u / PK] : rotate_8_rows(f.a[u / PK]));
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        acc[j] = mfma16x16x32(a, __builtin_bit_cast(f16x8, WBF16 ? bf16x8_to_f16x8(f.w[u][j]) : f.w[u][j]), acc[j]);
+    }
+  };
+  if (kb < ke) {
+    load(f0, kb);
+    for (int k = kb; k < ke; k += 2 * U) {
+      if (k + U < ke) load(f1, k + U);
+      mul(f0, k);
+      if (k + 2 * U < ke) load(f0, k + 2 * U);
+      if (k + U < ke) mul(f1, k + U);
+    }
+  }
+
+#pragma unroll
+  for (int j = 0; j < NT; ++j) red[wave][j][lane] = acc[j];
+  __syncthreads();
+  if (wave > 0) return;
+  // lane holds C[4la + r][16 blockIdx.x + li]
+  f32x4 v[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    v[j] = acc[j];
+    for (int w = 1; w < NW; ++w) v[j] += red[w][j][lane];
+  }
+  bool oor = false;
+  const int n = 16 * blockIdx.x + li;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int m = 4 * la + r;
+    if (m >= p.M) continue;
+    if (EPI == kEpiSwiglu) {
+      const float s = silu(v[0][r]) * v[NT - 1][r];
+      oor |= !(fabsf(s) <= 65504.0f);
+      ((f16*)p.c)[(int64_t)m * p.ldc + n] = (f16)s;
+    } else {
+      float x = v[0][r];
+      if (EPI == kEpiResidRow)
+        x += (float)((const bf16*)p.r)[(int64_t)(m % p.r_mod) * p.r_ld + n];
+      else if (EPI == kEpiResidF32)
+        x += ((const float*)p.r)[(int64_t)m * p.r_ld + n];
+      else if (EPI == kEpiRowScale)
+        x *= ((const float*)p.r)[m];
+      ((float*)p.c)[(int64_t)m * p.ldc + n] = x;
+    }
+  }
+  if (EPI == kEpiSwiglu && __any(oor) && lane == 0 && p.status) atomicOr(p.status, kStatusRange);
+}
+
+template <int NW, int U, int PK, int EPI>
+hipError_t launch_rows(const GemmParams& p, hipStream_t s) {
+  constexpr int cols = EPI == kEpiSwiglu ? 32 : 16;
+  if (p.M < 1 || p.M > 16 / PK || p.K % 32 || p.N % cols) return hipErrorInvalidValue;
+  if (EPI != kEpiSwiglu && (p.b_split0 % 16 || p.b_split1 % 16)) return hipErrorInvalidValue;
+  const dim3 block(64 * NW), grid(p.N / cols);
+  if (p.b_f16) hipLaunchKernelGGL((gemm_rows<NW, U, PK, EPI, false>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((gemm_rows<NW, U, PK, EPI, true>), grid, block, 0, s, p);
+  return hipGetLastError();
+}
+
+// Up to 8 rows: packed A fragments.  The wave counts and depths are the fastest
+// measured of 2-16 waves, 4 or 8 steps and one or two weight tiles.
+template <int EPI>
+hipError_t launch_rows_any(const GemmParams& p, hipStream_t s) {
+  if constexpr (EPI == kEpiSwiglu) return p.M <= 8 ? launch_rows<4, 4, 2, EPI>(p, s) : launch_rows<4, 4, 1, EPI>(p, s);
+  else return p.M <= 8 ? launch_rows<4, 8, 2, EPI>(p, s) : launch_rows<8, 4, 1, EPI>(p, s);
+}
+
+hipError_t launch_gemm_rows(Epilogue epi, const GemmParams& p, hipStream_t s) {
+  switch (epi) {
+    case kEpiStore: return launch_rows_any<kEpiStore>(p, s);
+    case kEpiResidRow: return launch_rows_any<kEpiResidRow>(p, s);
+    case kEpiResidF32: return launch_rows_any<kEpiResidF32>(p, s);
+    case kEpiRowScale: return launch_rows_any<kEpiRowScale>(p, s);
+    case kEpiSwiglu: return launch_rows_any<kEpiSwiglu>(p, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 // ---------------------------------------------------------------- fp32 path
 // One thread per output, the dot product in order k = 0..K-1.
 template <int EPI>
@@ -517,6 +668,14 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // tiles (8 row tiles by 4 column tiles with 32 compute units per XCD)
   if (p.group_m < 1) p.group_m = 8;
   auto fits = [&](int ks) { return p.part && (size_t)ks * p.M * p.N * sizeof(float) <= p.part_bytes; };
+  // Up to 16 rows: SwiGLU, and the other products with at most one 16-column
+  // tile per compute unit, on gemm_rows.  Wider products keep the one-wave tiles
+  // below: their tiles do not divide evenly over the compute units either way,
+  // and one wave each balances better (5 rows: 6144 x 4096 12.5 us against 13.5,
+  // 5120 x 17408 42.0 us against 47.9).
+  if (p.M <= 16 && (epi == kEpiSwiglu || p.N / 16 <= cus) && p.N % (epi == kEpiSwiglu ? 32 : 16) == 0 &&
+      (epi == kEpiSwiglu || (p.b_split0 % 16 == 0 && p.b_split1 % 16 == 0)))
+    return launch_gemm_rows(epi, p, s);
   // 17..32 rows: the product streams the weights; a 32-row by 128-column tile
   // with four waves, and K split so that the grid has enough workgroups in
   // flight (each slice at least 8 steps of 64).  (Up to 16 rows the one-wave
