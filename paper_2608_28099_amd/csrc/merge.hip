@@ -194,16 +194,23 @@ __global__ __launch_bounds__(256) void merge_splits(const MergeParams p) {
 // from the soft operands.  O^T lands with lane l holding dims 16 dt + 4(l/16) + r
 // of row l%16, which is also how it reads that row's split partials (16 bytes
 // per dim tile) and writes its fp16 output (8 bytes).
-template <int HD>
-__global__ __launch_bounds__(256) void merge_soft_mfma(const MergeParams p) {
+// SW > 1 (plans of many splits, which small batches of long contexts have): one
+// tile per workgroup, its SW waves each fold every SW-th split (wave 0 the soft
+// keys too), and the waves' (M, L, O) are combined through LDS in wave order.  A
+// single wave folds the splits one load round trip after another: one sequence of
+// 65536 tokens in 64 splits took 43.6 us, with eight waves 9 us.
+template <int HD, int SW>
+__global__ __launch_bounds__(SW == 1 ? 256 : 64 * SW) void merge_soft_mfma(const MergeParams p) {
   constexpr int NC = HD / 32, NDT = HD / 16;
+  constexpr int TPW = SW == 1 ? 4 : 1;  // query tiles per workgroup
   extern __shared__ uint16_t vt[];  // [2][HD][ldk] bf16 bits: V^T hi, then lo
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, la = lane >> 4;
   const int g = blockIdx.y, b = blockIdx.z;
   if (p.err && *p.err) return;
   const int R = p.q_per_task * p.group;
-  const int tiles = (R + 15) >> 4, wpt = (tiles + 3) >> 2;  // query tiles, workgroups per task
-  const int task = blockIdx.x / wpt, t = (blockIdx.x % wpt) * 4 + wave;
+  const int tiles = (R + 15) >> 4, wpt = (tiles + TPW - 1) / TPW;  // query tiles, workgroups per task
+  const int task = blockIdx.x / wpt, t = (blockIdx.x % wpt) * TPW + (SW == 1 ? wave : 0);
+  const int sw = SW == 1 ? 0 : wave;  // this wave folds splits sw, sw + SW, ...
   const int j_lo = task * p.k_task;
   const int nk_all = p.q_first + p.q_per_task + p.step;  // keys [j_lo, j_lo + nk_all)
   const int nkp = (nk_all + 31) & ~31, ldk = nkp + 4;
@@ -230,7 +237,7 @@ __global__ __launch_bounds__(256) void merge_soft_mfma(const MergeParams p) {
   float2 ml_pre[kMl];
 #pragma unroll
   for (int sp = 0; sp < kMl; ++sp)
-    if (t < tiles && sp < ns) ml_pre[sp] = p.ml_part[base + (int64_t)sp * p.r_alloc];
+    if (t < tiles && sw + SW * sp < ns) ml_pre[sp] = p.ml_part[base + (int64_t)(sw + SW * sp) * p.r_alloc];
 
   // stage V^T: consecutive lanes take consecutive keys of one 8-dim chunk
   const int64_t vo = (((p.per_seq ? (int64_t)b * p.n_kv : 0) + g) * p.ks + j_lo) * HD;
@@ -250,102 +257,156 @@ __global__ __launch_bounds__(256) void merge_soft_mfma(const MergeParams p) {
   __syncthreads();
   if (t >= tiles) return;
 
-  const int64_t ko = (bg * p.ks + j_lo) * HD;
-  const int nkt = (nk_all + 15) >> 4;
-  f32x4 sc[4];
-#pragma unroll
-  for (int kt = 0; kt < 4; ++kt) {
-    sc[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (kt < nkt) {
-      const int key = min(16 * kt + li, nk_all - 1);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const bf16x8 kh = __builtin_bit_cast(bf16x8, ld16v((const bf16*)p.k_soft + ko + (int64_t)key * HD + 32 * c + 8 * la));
-        const bf16x8 kl = __builtin_bit_cast(bf16x8, ld16v((const bf16*)p.k_soft_lo + ko + (int64_t)key * HD + 32 * c + 8 * la));
-        sc[kt] = mfma16x16x32_bf16(kh, qh[c], sc[kt]);
-        sc[kt] = mfma16x16x32_bf16(kh, ql[c], sc[kt]);
-        sc[kt] = mfma16x16x32_bf16(kl, qh[c], sc[kt]);
-      }
-    }
-  }
-  // causal window of the row: keys [j_lo, j_lo + nk_r); key j_lo always visible
-  const int nk_r = p.q_first + (rr / p.group) % p.q_per_task + p.step + 1;
-  float M = kNegBig;
-#pragma unroll
-  for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (16 * kt + 4 * la + i < nk_r) M = fmaxf(M, sc[kt][i]);
-  M = fmaxf(M, __shfl_xor(M, 16));
-  M = fmaxf(M, __shfl_xor(M, 32));
-  float L = 0.f;
-#pragma unroll
-  for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float pv = 16 * kt + 4 * la + i < nk_r ? fast_exp2(sc[kt][i] - M) : 0.f;
-      sc[kt][i] = pv;
-      L += pv;
-    }
-  L += __shfl_xor(L, 16);
-  L += __shfl_xor(L, 32);
-
+  float M = kNegBig, L = 0.f;
   f32x4 o[NDT];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (SW == 1 || sw == 0) {
+    const int64_t ko = (bg * p.ks + j_lo) * HD;
+    const int nkt = (nk_all + 15) >> 4;
+    f32x4 sc[4];
 #pragma unroll
-  for (int c2 = 0; c2 < 2; ++c2) {
-    if (32 * c2 < nk_all) {
-      bf16x8 ph, pl;
+    for (int kt = 0; kt < 4; ++kt) {
+      sc[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (kt < nkt) {
+        const int key = min(16 * kt + li, nk_all - 1);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float pv = sc[2 * c2 + (i >> 2)][i & 3];
-        ph[i] = (bf16)pv;
-        pl[i] = (bf16)(pv - (float)ph[i]);
+        for (int c = 0; c < NC; ++c) {
+          const bf16x8 kh = __builtin_bit_cast(bf16x8, ld16v((const bf16*)p.k_soft + ko + (int64_t)key * HD + 32 * c + 8 * la));
+          const bf16x8 kl = __builtin_bit_cast(bf16x8, ld16v((const bf16*)p.k_soft_lo + ko + (int64_t)key * HD + 32 * c + 8 * la));
+          sc[kt] = mfma16x16x32_bf16(kh, qh[c], sc[kt]);
+          sc[kt] = mfma16x16x32_bf16(kh, ql[c], sc[kt]);
+          sc[kt] = mfma16x16x32_bf16(kl, qh[c], sc[kt]);
+        }
       }
+    }
+    // causal window of the row: keys [j_lo, j_lo + nk_r); key j_lo always visible
+    const int nk_r = p.q_first + (rr / p.group) % p.q_per_task + p.step + 1;
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) {
-        const uint16_t* vr = vt + (16 * dt + li) * ldk + 32 * c2 + 4 * la;
-        const u32x2 h0 = *reinterpret_cast<const u32x2*>(vr), h1 = *reinterpret_cast<const u32x2*>(vr + 16);
-        const u32x2 l0 = *reinterpret_cast<const u32x2*>(vr + HD * ldk);
-        const u32x2 l1 = *reinterpret_cast<const u32x2*>(vr + HD * ldk + 16);
-        const bf16x8 vh = __builtin_bit_cast(bf16x8, u32x4{h0.x, h0.y, h1.x, h1.y});
-        const bf16x8 vl = __builtin_bit_cast(bf16x8, u32x4{l0.x, l0.y, l1.x, l1.y});
-        o[dt] = mfma16x16x32_bf16(vh, ph, o[dt]);
-        o[dt] = mfma16x16x32_bf16(vh, pl, o[dt]);
-        o[dt] = mfma16x16x32_bf16(vl, ph, o[dt]);
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (16 * kt + 4 * la + i < nk_r) M = fmaxf(M, sc[kt][i]);
+    M = fmaxf(M, __shfl_xor(M, 16));
+    M = fmaxf(M, __shfl_xor(M, 32));
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float pv = 16 * kt + 4 * la + i < nk_r ? fast_exp2(sc[kt][i] - M) : 0.f;
+        sc[kt][i] = pv;
+        L += pv;
+      }
+    L += __shfl_xor(L, 16);
+    L += __shfl_xor(L, 32);
+
+#pragma unroll
+    for (int c2 = 0; c2 < 2; ++c2) {
+      if (32 * c2 < nk_all) {
+        bf16x8 ph, pl;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float pv = sc[2 * c2 + (i >> 2)][i & 3];
+          ph[i] = (bf16)pv;
+          pl[i] = (bf16)(pv - (float)ph[i]);
+        }
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+          const uint16_t* vr = vt + (16 * dt + li) * ldk + 32 * c2 + 4 * la;
+          const u32x2 h0 = *reinterpret_cast<const u32x2*>(vr), h1 = *reinterpret_cast<const u32x2*>(vr + 16);
+          const u32x2 l0 = *reinterpret_cast<const u32x2*>(vr + HD * ldk);
+          const u32x2 l1 = *reinterpret_cast<const u32x2*>(vr + HD * ldk + 16);
+          const bf16x8 vh = __builtin_bit_cast(bf16x8, u32x4{h0.x, h0.y, h1.x, h1.y});
+          const bf16x8 vl = __builtin_bit_cast(bf16x8, u32x4{l0.x, l0.y, l1.x, l1.y});
+          o[dt] = mfma16x16x32_bf16(vh, ph, o[dt]);
+          o[dt] = mfma16x16x32_bf16(vh, pl, o[dt]);
+          o[dt] = mfma16x16x32_bf16(vl, ph, o[dt]);
+        }
       }
     }
   }
-  if (!valid) return;
+  if (SW == 1 && !valid) return;
 
-  // the splits' partials, by the log-sum-exp rule (rr == r from here on)
+  // the splits' partials, by the log-sum-exp rule (SW = 1: rr == r from here on)
   float Mt = M;
 #pragma unroll
   for (int sp = 0; sp < kMl; ++sp)
-    if (sp < ns) Mt = fmaxf(Mt, ml_pre[sp].x);
-  for (int sp = kMl; sp < ns; ++sp) Mt = fmaxf(Mt, p.ml_part[base + (int64_t)sp * p.r_alloc].x);
+    if (sw + SW * sp < ns) Mt = fmaxf(Mt, ml_pre[sp].x);
+  for (int sp = sw + SW * kMl; sp < ns; sp += SW) Mt = fmaxf(Mt, p.ml_part[base + (int64_t)sp * p.r_alloc].x);
   const float a0 = fast_exp2(M - Mt);
   L *= a0;
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) o[dt] *= a0;
-  for (int sp = 0; sp < ns; ++sp) {
-    const int64_t row = base + (int64_t)sp * p.r_alloc;
-    float2 ml;
-    if (sp < kMl) {
+  if constexpr (SW == 1) {
+    for (int sp = 0; sp < ns; ++sp) {
+      const int64_t row = base + (int64_t)sp * p.r_alloc;
+      float2 ml;
+      if (sp < kMl) {
 #pragma unroll
-      for (int q = 0; q < kMl; ++q)
-        if (q == sp) ml = ml_pre[q];
-    } else {
-      ml = p.ml_part[row];
+        for (int q = 0; q < kMl; ++q)
+          if (q == sp) ml = ml_pre[q];
+      } else {
+        ml = p.ml_part[row];
+      }
+      const float w = ml.y * fast_exp2(ml.x - Mt);  // the partial is O_s / l_s
+      L += w;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) {
+        const f16x4 v = *reinterpret_cast<const f16x4*>((const f16*)p.o_part + row * HD + 16 * dt + 4 * la);
+        o[dt] += f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]} * w;
+      }
     }
-    const float w = ml.y * fast_exp2(ml.x - Mt);  // the partial is O_s / l_s
-    L += w;
+  } else {
+    // kMl splits' partials requested at once, then folded
+    for (int s0 = sw; s0 < ns; s0 += SW * kMl) {
+      float2 ml[kMl];
+      f16x4 v[kMl][NDT];
+#pragma unroll
+      for (int q = 0; q < kMl; ++q) {
+        if (s0 + SW * q < ns) {
+          const int64_t row = base + (int64_t)(s0 + SW * q) * p.r_alloc;
+          ml[q] = s0 == sw ? ml_pre[q] : p.ml_part[row];
+#pragma unroll
+          for (int dt = 0; dt < NDT; ++dt)
+            v[q][dt] = *reinterpret_cast<const f16x4*>((const f16*)p.o_part + row * HD + 16 * dt + 4 * la);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kMl; ++q) {
+        if (s0 + SW * q < ns) {
+          const float w = ml[q].y * fast_exp2(ml[q].x - Mt);
+          L += w;
+#pragma unroll
+          for (int dt = 0; dt < NDT; ++dt)
+            o[dt] += f32x4{(float)v[q][dt][0], (float)v[q][dt][1], (float)v[q][dt][2], (float)v[q][dt][3]} * w;
+        }
+      }
+    }
+    // combine the waves; wave w finishes dim tiles w, w + SW, ...
+    __shared__ f32x4 osh[SW][NDT][64];
+    __shared__ float2 mlsh[SW][64];
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) osh[wave][dt][lane] = o[dt];
+    mlsh[wave][lane] = make_float2(Mt, L);
+    __syncthreads();
+    float Mg = kNegBig;
+#pragma unroll
+    for (int w = 0; w < SW; ++w) Mg = fmaxf(Mg, mlsh[w][lane].x);
+    float wt[SW];
+    L = 0.f;
+#pragma unroll
+    for (int w = 0; w < SW; ++w) {
+      wt[w] = fast_exp2(mlsh[w][lane].x - Mg);
+      L += mlsh[w][lane].y * wt[w];
+    }
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) {
-      const f16x4 v = *reinterpret_cast<const f16x4*>((const f16*)p.o_part + row * HD + 16 * dt + 4 * la);
-      o[dt] += f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]} * w;
+      if (dt % SW != wave) continue;
+      o[dt] = osh[0][dt][lane] * wt[0];
+#pragma unroll
+      for (int w = 1; w < SW; ++w) o[dt] += osh[w][dt][lane] * wt[w];
     }
+    if (!valid) return;
   }
   const float inv = 1.0f / L;
   const int qi = task * p.q_per_task + r / p.group, h = g * p.group + r % p.group;
@@ -353,6 +414,7 @@ __global__ __launch_bounds__(256) void merge_soft_mfma(const MergeParams p) {
   bool oor = false;
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) {
+    if (SW > 1 && dt % SW != wave) continue;
     f16x4 y;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -362,7 +424,7 @@ __global__ __launch_bounds__(256) void merge_soft_mfma(const MergeParams p) {
     }
     *reinterpret_cast<f16x4*>(out + 16 * dt) = y;
   }
-  if (__any(oor) && lane == 0 && p.status) atomicOr(p.status, kStatusRange);
+  if (oor && p.status) atomicOr(p.status, kStatusRange);
 }
 
 }  // namespace
@@ -381,10 +443,19 @@ hipError_t launch_merge(DType dt, const MergeParams& p, int batch, hipStream_t s
   if (dt == kBF16) {
     const int R = p.q_per_task * p.group, tiles = (R + 15) / 16;
     const int nkp = (nk_max + 31) & ~31;
-    const dim3 grid(tasks * ((tiles + 3) / 4), p.n_kv, batch), block(64 * (tiles < 4 ? tiles : 4));
     const size_t lds = (size_t)2 * p.hd * (nkp + 4) * sizeof(uint16_t);
-    if (p.hd == 128) hipLaunchKernelGGL(merge_soft_mfma<128>, grid, block, lds, s, p);
-    else hipLaunchKernelGGL(merge_soft_mfma<64>, grid, block, lds, s, p);
+    // By the plan's split count alone, so that a sequence's result does not
+    // depend on the batch it comes in.  Plans of few splits (large batches) have
+    // waves enough with one per tile.
+    if (p.max_splits >= 8) {
+      const dim3 grid(tasks * tiles, p.n_kv, batch), block(512);
+      if (p.hd == 128) hipLaunchKernelGGL((merge_soft_mfma<128, 8>), grid, block, lds, s, p);
+      else hipLaunchKernelGGL((merge_soft_mfma<64, 8>), grid, block, lds, s, p);
+      return hipGetLastError();
+    }
+    const dim3 grid(tasks * ((tiles + 3) / 4), p.n_kv, batch), block(64 * (tiles < 4 ? tiles : 4));
+    if (p.hd == 128) hipLaunchKernelGGL((merge_soft_mfma<128, 1>), grid, block, lds, s, p);
+    else hipLaunchKernelGGL((merge_soft_mfma<64, 1>), grid, block, lds, s, p);
     return hipGetLastError();
   }
   // fp32 path.  Soft rows per workgroup: the most (a power of two) that still

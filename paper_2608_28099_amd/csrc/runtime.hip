@@ -50,6 +50,13 @@ constexpr uint32_t kImageMagic = 0x31504B53u;
 constexpr int kHeaderWords = 8;
 constexpr size_t kHeaderBytes = 256;
 
+// Workspace of the forward without a handle (a static device array).
+constexpr size_t kScratchBytes = size_t(64) << 20;
+
+// Shortest attention splits (tokens): of batches that fill the device in splits
+// of the first length, and of smaller ones (see attn_plan).
+constexpr int kCoarseSplit = 1024, kFineSplit = 256;
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
 int ilog2(int64_t x) { int r = 0; while ((int64_t(1) << r) < x) ++r; return r; }
@@ -95,6 +102,7 @@ struct AttnPlan {
 };
 
 struct Plan {
+  bool coarse;   // no short attention splits
   int group, max_tasks, ks, ks_rec, nqkv, esz, num_cus;
   int q_rows;    // query rows per (sequence, KV head) the one-pass query buffer holds
   AttnPlan rec;  // recursive steps: one soft row (G query rows) per KV head
@@ -148,7 +156,14 @@ int check_config(const sp_probe_config* c) {
   return SP_OK;
 }
 
-AttnPlan attn_plan(const sp_probe_config& c, int rows, int num_cus) {
+// Workgroups of the attention launch that the device holds at once (bf16 storage).
+int64_t attn_slots(const sp_probe_config& c, const AttnPlan& a, int num_cus) {
+  const int64_t per_cu = attn_wgs_per_cu(c.head_dim, a.waves, (a.tiles + a.waves - 1) / a.waves);
+  return (int64_t)num_cus * std::max<int64_t>(per_cu, 1);
+}
+
+// coarse: no bf16 split shorter than kCoarseSplit tokens (see make_plan).
+AttnPlan attn_plan(const sp_probe_config& c, int rows, int num_cus, bool coarse) {
   AttnPlan a{};
   a.rows = rows;
   const int tiles = (rows + 15) / 16;
@@ -193,13 +208,25 @@ AttnPlan attn_plan(const sp_probe_config& c, int rows, int num_cus) {
     // sequence: three splits for the longest sequences measured faster than
     // one, two or four on uniform and ragged batches alike, whether the grid
     // is one round or many.  At least 1024 tokens, a multiple of 256.
-    const int64_t per_cu = attn_wgs_per_cu(c.head_dim, a.waves, (a.tiles + a.waves - 1) / a.waves);
-    const int64_t slots = (int64_t)num_cus * std::max<int64_t>(per_cu, 1);
+    const int64_t slots = attn_slots(c, a, num_cus);
     const int64_t items = (int64_t)c.max_batch * c.n_kv_heads * a.n_qgroups;
     const int64_t want = ((int64_t)c.max_seq_len * items + slots - 1) / slots;
     const int64_t third = ((int64_t)c.max_seq_len + 2) / 3;
     const int64_t sl = (std::min(want, third) + 255) / 256 * 256;
-    a.split_len = (int)std::max<int64_t>(sl, 1024);
+    a.split_len = (int)std::max<int64_t>(sl, kCoarseSplit);
+    // A batch too small to fill the round in splits of 1024 tokens takes the
+    // length that fills it, at least 256: 2048 tokens of one sequence over 8 KV
+    // heads in eight splits of 256 (forward 125 us, 147 in two of 1024), nine
+    // ragged sequences of up to 3000 in ten splits of 320 (recursive SP-2 287 us
+    // against 321).  A single sequence has no raggedness to balance and fills two
+    // workgroups per compute unit (65536 tokens: 64 splits 138 us per forward, 94
+    // splits 142).
+    const int64_t fill = c.max_batch == 1 ? std::min<int64_t>(slots, 2 * (int64_t)num_cus) : slots;
+    const int64_t grid = items * (((int64_t)c.max_seq_len + kCoarseSplit - 1) / kCoarseSplit);
+    if (!coarse && grid < fill) {
+      const int64_t len = ((int64_t)c.max_seq_len * items + fill - 1) / fill;
+      a.split_len = (int)std::max<int64_t>((len + 63) / 64 * 64, kFineSplit);
+    }
   } else {
     // fp32 path: at most 8 splits per sequence, between 1024 and 16384 tokens each
     int sl = 1024;
@@ -214,19 +241,20 @@ int n_tasks_max(const sp_probe_config& c) { return c.max_tasks > 0 ? c.max_tasks
 
 // Attention plan of a one-pass forward with n_tasks tasks: k G query rows per
 // task and KV head, or G under SP_FLAG_LAST_ROW_ONLY.
-AttnPlan one_pass_plan(const sp_probe_config& c, int n_tasks, int num_cus) {
+AttnPlan one_pass_plan(const sp_probe_config& c, int n_tasks, int num_cus, bool coarse) {
   const int group = c.n_q_heads / c.n_kv_heads;
   const int per_task = (c.flags & SP_FLAG_LAST_ROW_ONLY) ? 1 : c.k;
-  return attn_plan(c, n_tasks * per_task * group, num_cus);
+  return attn_plan(c, n_tasks * per_task * group, num_cus, coarse);
 }
 
-Plan make_plan(const sp_probe_config& c, int num_cus) {
+Plan make_plan(const sp_probe_config& c, int num_cus, bool coarse) {
   Plan p{};
   p.num_cus = num_cus;
+  p.coarse = coarse;
   p.esz = c.dtype == SP_BF16 ? 2 : 4;
   p.group = c.n_q_heads / c.n_kv_heads;
   p.max_tasks = n_tasks_max(c);
-  p.rec = attn_plan(c, p.group, num_cus);
+  p.rec = attn_plan(c, p.group, num_cus, coarse);
   const int S = p.max_tasks * c.k;       // soft rows of the largest call
   p.ks = ((S + 31) / 32) * 32;
   p.ks_rec = ((c.k + 31) / 32) * 32;
@@ -236,7 +264,7 @@ Plan make_plan(const sp_probe_config& c, int num_cus) {
   p.q_rows = 0;
   p.items_splits = p.rec.max_splits;
   for (int t = 1; t <= p.max_tasks; ++t) {
-    const AttnPlan a = one_pass_plan(c, t, num_cus);
+    const AttnPlan a = one_pass_plan(c, t, num_cus, coarse);
     part_rows = std::max(part_rows, (size_t)a.max_splits * a.r_alloc);
     p.q_rows = std::max(p.q_rows, a.r_alloc);
     p.items_splits = std::max(p.items_splits, a.max_splits);
@@ -298,6 +326,15 @@ Plan make_plan(const sp_probe_config& c, int num_cus) {
   p.off_guard_tab = take(kMaxGuards * sizeof(uint64_t));
   p.total = o;
   return p;
+}
+
+// The plan of a handle, and of the call without one: short splits where they pay,
+// unless only the coarse plan's smaller workspace fits the static scratch.
+Plan make_plan(const sp_probe_config& c, int num_cus) {
+  const Plan fine = make_plan(c, num_cus, false);
+  if (fine.total <= kScratchBytes) return fine;
+  const Plan coarse = make_plan(c, num_cus, true);
+  return coarse.total <= kScratchBytes ? coarse : fine;
 }
 
 // Compute units of the current device, or kDefaultCus when none can be asked.
@@ -455,6 +492,14 @@ int check_forward(const sp_probe_config& c, const Plan& pl, const sp_kv_cache* k
   return SP_OK;
 }
 
+// Whether the attention takes its items from a work list (bf16 storage): a grid
+// of at most one round of resident workgroups starts all at once, so an order
+// would only cost its launch (4.5 us) and each workgroup a dependent load.
+bool needs_work_list(const Ctx& x, const AttnPlan& a, int batch) {
+  return x.cfg->dtype == SP_BF16 && (int64_t)x.cfg->n_kv_heads * a.n_qgroups * a.max_splits * batch >
+                                        attn_slots(*x.cfg, a, x.n_cus);
+}
+
 // Split-attention parameters over the caller's cache for one attention plan.
 AttnParams attn_params(const Ctx& x, const AttnPlan& a, const sp_kv_cache* kv,
                        const int32_t* seq_lens, const int32_t* block_table, const int* errp,
@@ -478,9 +523,10 @@ AttnParams attn_params(const Ctx& x, const AttnPlan& a, const sp_kv_cache* kv,
   ap.num_cus = x.n_cus;
   ap.f16 = a.f16;
   ap.stages = 3;
-  // bf16 path: the work list launch_work_list wrote for this plan
-  ap.items = c.dtype == SP_BF16 ? at<int2>(x, x.plan->off_items) : nullptr;
-  ap.n_items = c.dtype == SP_BF16 ? at<int>(x, x.plan->off_n_items) : nullptr;
+  // the work list launch_work_list wrote for this plan
+  const bool list = needs_work_list(x, a, kv->batch);
+  ap.items = list ? at<int2>(x, x.plan->off_items) : nullptr;
+  ap.n_items = list ? at<int>(x, x.plan->off_n_items) : nullptr;
   return ap;
 }
 
@@ -626,7 +672,7 @@ void write_plan(const AttnPlan& a, int32_t* split_len, int32_t* max_splits, int3
 SP_API int sp_probe_plan(const sp_probe_t* h, int32_t batch, int32_t* split_len, int32_t* max_splits,
                          int32_t* rows_per_kv_head, int32_t* query_groups) {
   if (!h || batch < 0) return SP_ERR_INVALID_ARG;
-  write_plan(one_pass_plan(h->cfg, 1, h->num_cus), split_len, max_splits, rows_per_kv_head, query_groups);
+  write_plan(one_pass_plan(h->cfg, 1, h->num_cus, h->plan.coarse), split_len, max_splits, rows_per_kv_head, query_groups);
   return SP_OK;
 }
 
@@ -644,8 +690,9 @@ SP_API int sp_probe_plan_config(const sp_probe_config* cfg, int32_t num_cus, int
   const int st = check_config(cfg);
   if (st != SP_OK) return st;
   if (num_cus < 1 || num_cus > 65536) return SP_ERR_INVALID_ARG;
-  write_plan(one_pass_plan(*cfg, 1, num_cus), split_len, max_splits, rows_per_kv_head, query_groups);
-  if (workspace_bytes) *workspace_bytes = make_plan(*cfg, num_cus).total;
+  const Plan pl = make_plan(*cfg, num_cus);
+  write_plan(one_pass_plan(*cfg, 1, num_cus, pl.coarse), split_len, max_splits, rows_per_kv_head, query_groups);
+  if (workspace_bytes) *workspace_bytes = pl.total;
   return SP_OK;
 }
 
@@ -717,7 +764,7 @@ int forward_one_pass(const Ctx& x, const sp_kv_cache* kv, const int32_t* seq_len
   const int Kq = last_only ? 1 : K;          // rows per task past the attention
   const int R = n_tasks * Kq;                // rows per sequence past the attention
   const int M = B * R;
-  const AttnPlan ak = one_pass_plan(c, n_tasks, x.n_cus);
+  const AttnPlan ak = one_pass_plan(c, n_tasks, x.n_cus, pl.coarse);
   const ProjW pw = proj_weights(c, wt);
   const bool debug = c.flags & SP_FLAG_DEBUG;
   int* err = at<int>(x, pl.off_err);
@@ -769,7 +816,7 @@ int forward_one_pass(const Ctx& x, const sp_kv_cache* kv, const int32_t* seq_len
                                     at<float2>(x, pl.off_ml));
   if (dt == kBF16) {
     if (ak.max_splits > pl.items_splits) return SP_ERR_INTERNAL;
-    SP_TRY(launch_work_list(seq_lens, B, c.max_seq_len, ak.split_len, at<int2>(x, pl.off_items),
+    if (ap.items) SP_TRY(launch_work_list(seq_lens, B, c.max_seq_len, ak.split_len, at<int2>(x, pl.off_items),
                             at<int>(x, pl.off_n_items), s));
     SP_TRY(launch_attention_bf16(ap, hd, ak.waves, B, s));
   } else {
@@ -941,7 +988,7 @@ SP_API int sp_probe_forward_recursive(sp_probe_t* h, const sp_kv_cache* kv, cons
   }
 
   // the attention of every step runs the same work list, longest items first
-  if (dt == kBF16) {
+  if (dt == kBF16 && needs_work_list(x, rp, B)) {
     if (pl.rec.max_splits > pl.items_splits) return SP_ERR_INTERNAL;
     SP_TRY(launch_work_list(seq_lens, B, c.max_seq_len, pl.rec.split_len, at<int2>(x, pl.off_items),
                             at<int>(x, pl.off_n_items), s));
@@ -1146,7 +1193,6 @@ SP_API int sp_probe_profile_read(sp_probe_t* h, float* stage_ms, int32_t n_stage
 // address on the host.
 namespace {
 
-constexpr size_t kScratchBytes = size_t(64) << 20;
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
