@@ -96,6 +96,12 @@ __device__ __forceinline__ f32x4 mfma16x16x16(f16x4 a, f16x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0);
 }
 
+// D(16x16, fp32) += A(16x4, fp32) * B(4x16, fp32), fp32 products.
+// Lane l holds A[l%16][l/16], B[l/16][l%16]; D as above.
+__device__ __forceinline__ f32x4 mfma16x16x4_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Block-wide sum for blockDim.x == 256 (4 waves); `red` holds >= 4 floats.

@@ -365,36 +365,114 @@ hipError_t launch_gemm_rows(Epilogue epi, const GemmParams& p, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- fp32 path
-// One thread per output, the dot product in order k = 0..K-1.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32(const GemmParams p) {
-  const int n = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y;
+// C = A W^T in fp32 throughout (fp32 matrix-core products, whose A and B fragments
+// are one value per lane).  One workgroup takes 16 MT rows by 16 outputs (SwiGLU: 16
+// gate and the 16 matching up rows of W) over the whole of K, its NW waves
+// contiguous slices of K, summed in wave order through LDS, as gemm_rows does.
+// Lane (li, la) loads four consecutive k of row li (16 bytes) and element e feeds
+// product e: the four lanes of a product then hold k = 16 j + 4 la + e of step j, the
+// same k in A and W.  The small fp32 heads are bound by latency: a thread per
+// output walking K took 35-124 us a product on 16 rows (256 to 1024 deep), this
+// 3-5 us.
+template <int MT, int NW, int EPI>
+__global__ __launch_bounds__(64 * NW) void gemm_f32(const GemmParams p) {
+  constexpr int NT = EPI == kEpiSwiglu ? 2 : 1, U = 4;
+  __shared__ f32x4 red[NW][MT * NT][64];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, la = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_out = EPI == kEpiSwiglu ? p.N / 2 : p.N;
-  if (n >= n_out) return;
-  const float* a = (const float*)p.a + (int64_t)m * p.lda;
-  auto row = [&](int nn) -> const float* {
-    if (nn < p.b_split0) return (const float*)p.b[0] + (int64_t)nn * p.ldb;
-    if (nn < p.b_split1) return (const float*)p.b[1] + (int64_t)(nn - p.b_split0) * p.ldb;
-    return (const float*)p.b[2] + (int64_t)(nn - p.b_split1) * p.ldb;
-  };
-  if (EPI == kEpiSwiglu) {
-    const float* wg = (const float*)p.b[0] + (int64_t)n * p.ldb;
-    const float* wu = (const float*)p.b[1] + (int64_t)n * p.ldb;
-    float g = 0.f, u = 0.f;
-    for (int k = 0; k < p.K; ++k) {
-      g += a[k] * wg[k];
-      u += a[k] * wu[k];
-    }
-    ((float*)p.c)[(int64_t)m * p.ldc + n] = g / (1.0f + expf(-g)) * u;
-    return;
+  const int n0 = 16 * blockIdx.x, m0 = 16 * MT * blockIdx.y;
+  const int KT = (p.K + 15) / 16, kb = KT * wave / NW, ke = KT * (wave + 1) / NW;
+
+  const float* ap[MT];
+  const float* wp[NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)  // rows past M and outputs past n_out re-read the last; never stored
+    ap[i] = (const float*)p.a + (int64_t)min(m0 + 16 * i + li, p.M - 1) * p.lda;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int n = min(n0 + li, n_out - 1);
+    const int src = EPI == kEpiSwiglu ? j : n < p.b_split0 ? 0 : (n < p.b_split1 ? 1 : 2);
+    const int row = n - (EPI == kEpiSwiglu || src == 0 ? 0 : (src == 1 ? p.b_split0 : p.b_split1));
+    const void* b = src == 0 ? p.b[0] : (src == 1 ? p.b[1] : p.b[2]);
+    wp[j] = (const float*)b + (int64_t)row * p.ldb;
   }
-  const float* w = row(n);
-  float acc = 0.f;
-  for (int k = 0; k < p.K; ++k) acc += a[k] * w[k];
-  if (EPI == kEpiResidRow) acc += ((const float*)p.r)[(int64_t)(m % p.r_mod) * p.r_ld + n];
-  if (EPI == kEpiResidF32) acc += ((const float*)p.r)[(int64_t)m * p.r_ld + n];
-  if (EPI == kEpiRowScale) acc *= ((const float*)p.r)[m];
-  ((float*)p.c)[(int64_t)m * p.ldc + n] = acc;
+
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = kb; k0 < ke; k0 += U) {
+    f32x4 a[U][MT], w[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = 16 * (k0 + u) + 4 * la;
+      const bool in = k0 + u < ke && k < p.K;  // K % 4 == 0: a lane's four k are all in or all out
+      const int kk = in ? k : 0;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        w[u][j] = *reinterpret_cast<const f32x4*>(wp[j] + kk);
+        if (!in) w[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        a[u][i] = *reinterpret_cast<const f32x4*>(ap[i] + kk);
+        if (!in) a[u][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) acc[i][j] = mfma16x16x4_f32(a[u][i][e], w[u][j][e], acc[i][j]);
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) red[wave][i * NT + j][lane] = acc[i][j];
+  __syncthreads();
+
+  // lane holds C[m0 + 16i + 4la + r][n0 + li]; wave w finishes row tiles w, w + NW, ...
+  const int n = n0 + li;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    if (i % NW != wave || n >= n_out) continue;
+    f32x4 v[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      v[j] = red[0][i * NT + j][lane];
+      for (int w = 1; w < NW; ++w) v[j] += red[w][i * NT + j][lane];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + 16 * i + 4 * la + r;
+      if (m >= p.M) continue;
+      float x = v[0][r];
+      if (EPI == kEpiSwiglu) x = x / (1.0f + expf(-x)) * v[NT - 1][r];
+      if (EPI == kEpiResidRow) x += ((const float*)p.r)[(int64_t)(m % p.r_mod) * p.r_ld + n];
+      if (EPI == kEpiResidF32) x += ((const float*)p.r)[(int64_t)m * p.r_ld + n];
+      if (EPI == kEpiRowScale) x *= ((const float*)p.r)[m];
+      ((float*)p.c)[(int64_t)m * p.ldc + n] = x;
+    }
+  }
+}
+
+// Four row tiles per workgroup (each weight fragment then serves 64 rows) where
+// that still leaves a workgroup per compute unit, else one.
+template <int EPI>
+hipError_t launch_f32(const GemmParams& p, hipStream_t s) {
+  if (p.K % 4 || p.lda % 4 || p.ldb % 4 || p.M > 16 * 65535) return hipErrorInvalidValue;
+  const int n_out = EPI == kEpiSwiglu ? p.N / 2 : p.N, cols = (n_out + 15) / 16;
+  const int cus = p.n_cus > 0 ? p.n_cus : 256;
+  if (p.M > 16 && (int64_t)cols * ((p.M + 63) / 64) >= cus)
+    hipLaunchKernelGGL((gemm_f32<4, 8, EPI>), dim3(cols, (p.M + 63) / 64), dim3(512), 0, s, p);
+  else
+    hipLaunchKernelGGL((gemm_f32<1, 8, EPI>), dim3(cols, (p.M + 15) / 16), dim3(512), 0, s, p);
+  return hipGetLastError();
 }
 
 // Sum of the split-K slices and the epilogue, one thread per output.  SwiGLU:
@@ -648,17 +726,14 @@ static int whole_round_columns(const GemmParams& p, int cus, double other, doubl
 hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t s) {
   if (p0.M <= 0) return hipSuccess;
   if (dt == kF32) {
-    const GemmParams& p = p0;
-    const int n_out = epi == kEpiSwiglu ? p.N / 2 : p.N;
-    const dim3 grid((n_out + 255) / 256, p.M);
     switch (epi) {
-      case kEpiStore: hipLaunchKernelGGL(gemm_f32<kEpiStore>, grid, dim3(256), 0, s, p); break;
-      case kEpiResidRow: hipLaunchKernelGGL(gemm_f32<kEpiResidRow>, grid, dim3(256), 0, s, p); break;
-      case kEpiResidF32: hipLaunchKernelGGL(gemm_f32<kEpiResidF32>, grid, dim3(256), 0, s, p); break;
-      case kEpiRowScale: hipLaunchKernelGGL(gemm_f32<kEpiRowScale>, grid, dim3(256), 0, s, p); break;
-      case kEpiSwiglu: hipLaunchKernelGGL(gemm_f32<kEpiSwiglu>, grid, dim3(256), 0, s, p); break;
+      case kEpiStore: return launch_f32<kEpiStore>(p0, s);
+      case kEpiResidRow: return launch_f32<kEpiResidRow>(p0, s);
+      case kEpiResidF32: return launch_f32<kEpiResidF32>(p0, s);
+      case kEpiRowScale: return launch_f32<kEpiRowScale>(p0, s);
+      case kEpiSwiglu: return launch_f32<kEpiSwiglu>(p0, s);
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
   }
   if (p0.K % 32 || p0.lda % 8 || p0.ldb % 8) return hipErrorInvalidValue;
   GemmParams p = p0;

@@ -99,7 +99,7 @@ inline int attn_wgs_per_cu(int hd, int waves, int tiles_per_wave = 1) {
 // bf16-storage path (bf16 MFMA, split Q and P): head_dim 64/128, `waves` 16-row
 // query tiles per workgroup (1, 2, 3, 4, 5, 6, 8, 10 or 12; up to 16 for head_dim 64).
 hipError_t launch_attention_bf16(const AttnParams& p, int hd, int waves, int batch, hipStream_t s);
-// fp32 VALU path: head_dim 64/128, rows <= 64.
+// fp32 path (fp32 matrix-core products): head_dim 64/128, rows <= 64.
 hipError_t launch_attention_f32(const AttnParams& p, int hd, int batch, hipStream_t s);
 // The split attention's work items in dispatch order (longest first): every
 // split that is not its sequence's last (split_len tokens each), by sequence
@@ -162,7 +162,7 @@ struct GemmParams {
   int n_cus, n_xcd;        // compute units and XCDs of the device
   int group_m;             // row tiles per group of the tile order (0: the launcher's choice)
 };
-// dt: storage dtype of the weights (kF32: fp32 VALU path; kBF16: fp16 MFMA path)
+// dt: storage dtype of the weights (kF32: fp32 matrix-core path; kBF16: fp16 MFMA path)
 hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p, hipStream_t s);
 // One tile shape of the fp16 MFMA path (index into the tile table of gemm.hip),
 // K split ksplit ways: for measurement; launch_gemm chooses for the forward.

@@ -228,9 +228,14 @@ AttnPlan attn_plan(const sp_probe_config& c, int rows, int num_cus, bool coarse)
       a.split_len = (int)std::max<int64_t>((len + 63) / 64 * 64, kFineSplit);
     }
   } else {
-    // fp32 path: at most 8 splits per sequence, between 1024 and 16384 tokens each
+    // fp32 path: at most 8 splits per sequence, between 1024 and 16384 tokens
+    // each; shorter ones (256 tokens or more) where a small batch leaves compute
+    // units without a workgroup.
     int sl = 1024;
     while (sl < 16384 && (int64_t)sl * 8 < c.max_seq_len) sl *= 2;
+    const int64_t items = (int64_t)c.max_batch * c.n_kv_heads * tiles;
+    const int64_t len = ((int64_t)c.max_seq_len * items + num_cus - 1) / num_cus;
+    if (!coarse) sl = (int)std::min<int64_t>(sl, std::max<int64_t>((len + 63) / 64 * 64, kFineSplit));
     a.split_len = sl;
   }
   a.max_splits = c.max_seq_len > 0 ? (c.max_seq_len + a.split_len - 1) / a.split_len : 1;
