@@ -681,72 +681,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_split_f32(const AttnParam
   }
 }
 
-// One workgroup of 1024 threads: the work list (see launch_work_list).  Full
-// splits: an exclusive scan of (splits - 1) per sequence, 1024 sequences at a
-// time; last splits: the rank of each by (tokens descending, sequence), the
-// candidates staged 1024 at a time in LDS.
-__global__ __launch_bounds__(1024) void work_list(const int* seq_lens, int batch, int max_seq_len, int split_len,
-                                                  int2* items, int* count) {
-  __shared__ __align__(16) int scan[1024];
-  __shared__ int carry;
-  const int tid = threadIdx.x;
-  auto splits = [&](int b) { const int n = clamp_len(seq_lens, b, max_seq_len); return n > 0 ? (n + split_len - 1) / split_len : 1; };
-  auto last_tokens = [&](int b) { const int n = clamp_len(seq_lens, b, max_seq_len); return n - (splits(b) - 1) * split_len; };
-  if (tid == 0) carry = 0;
-  __syncthreads();
-  for (int b0 = 0; b0 < batch; b0 += 1024) {
-    const int b = b0 + tid;
-    const int nf = b < batch ? splits(b) - 1 : 0;
-    scan[tid] = nf;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-      const int v = tid >= o ? scan[tid - o] : 0;
-      __syncthreads();
-      scan[tid] += v;
-      __syncthreads();
-    }
-    const int off = carry + scan[tid] - nf;
-    for (int sp = 0; sp < nf; ++sp) items[off + sp] = make_int2(b, sp);
-    __syncthreads();
-    if (tid == 1023) carry += scan[1023];
-    __syncthreads();
-  }
-  const int full = carry;
-  for (int b0 = 0; b0 < batch; b0 += 1024) {
-    const int b = b0 + tid;
-    const int rb = b < batch ? last_tokens(b) : 0;
-    int rank = 0;
-    for (int o0 = 0; o0 < batch; o0 += 1024) {
-      __syncthreads();
-      scan[tid] = o0 + tid < batch ? last_tokens(o0 + tid) : -1;  // -1: no sequence (ranks below all)
-      __syncthreads();
-      // four counts per 16-byte LDS read (the slots past the batch hold -1)
-      const int m4 = (min(1024, batch - o0) + 3) / 4;
-      const int4* s4 = (const int4*)scan;
-#pragma unroll 4
-      for (int q = 0; q < m4; ++q) {
-        const int4 r = s4[q];
-        const int j = o0 + 4 * q;
-        rank += (r.x > rb) || (r.x == rb && j < b);
-        rank += (r.y > rb) || (r.y == rb && j + 1 < b);
-        rank += (r.z > rb) || (r.z == rb && j + 2 < b);
-        rank += (r.w > rb) || (r.w == rb && j + 3 < b);
-      }
-    }
-    if (b < batch) items[full + rank] = make_int2(b, splits(b) - 1);
-  }
-  if (tid == 0) count[0] = full + batch;
-}
-
 }  // namespace
-
-hipError_t launch_work_list(const int* seq_lens, int batch, int max_seq_len, int split_len, int2* items, int* count,
-                            hipStream_t s) {
-  if (batch <= 0) return hipSuccess;
-  if (split_len < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(work_list, dim3(1), dim3(1024), 0, s, seq_lens, batch, max_seq_len, split_len, items, count);
-  return hipGetLastError();
-}
 
 hipError_t launch_attention_bf16(const AttnParams& p, int hd, int waves, int batch, hipStream_t s) {
   const bool f16 = p.f16;

@@ -46,9 +46,18 @@ struct RopeParams {
   int step;                // position and slot offset (recursive step)
   int per_seq;             // projections and values per sequence (recursive steps)
   int k_task, q_first, q_per_task;
-  double rope_base;
+  double rope_base, log2_base;  // the RoPE base and its log2
   float q_scale;           // log2(e) / sqrt(hd)
   int num_cus;             // compute units of the device (sizes the grid)
+  // nullable: the launch also writes the split attention's work items in
+  // dispatch order (longest first) for splits of split_len tokens: every split
+  // that is not its sequence's last (split_len tokens each), by sequence and
+  // split; then each sequence's last split (split 0 of an empty sequence), by
+  // token count descending, ties by sequence.  items holds batch * (splits of
+  // max_seq_len) pairs (sequence, split); *n_items receives the number written.
+  int2* items;
+  int* n_items;
+  int split_len;
 };
 // dt: output type: kF32, or kBF16 for the hi/lo bf16 split
 hipError_t launch_rope_scatter(DType dt, const RopeParams& p, int batch, hipStream_t s);
@@ -68,7 +77,7 @@ struct AttnParams {
   int64_t k_sb, k_sh, v_sb, v_sh;     // elements
   const int* block_table;  // nullable (contiguous)
   const int* seq_lens;
-  // nullable (bf16 path: from launch_work_list): the (sequence, split) of grid
+  // nullable (bf16 path: from launch_rope_scatter): the (sequence, split) of grid
   // slot y + max_splits z, for the first *n_items slots; later slots exit
   const int2* items;
   const int* n_items;
@@ -101,14 +110,6 @@ inline int attn_wgs_per_cu(int hd, int waves, int tiles_per_wave = 1) {
 hipError_t launch_attention_bf16(const AttnParams& p, int hd, int waves, int batch, hipStream_t s);
 // fp32 path (fp32 matrix-core products): head_dim 64/128, rows <= 64.
 hipError_t launch_attention_f32(const AttnParams& p, int hd, int batch, hipStream_t s);
-// The split attention's work items in dispatch order (longest first): every
-// split that is not its sequence's last (split_len tokens each), by sequence
-// and split; then each sequence's last split (split 0 of an empty sequence),
-// by token count descending, ties by sequence.  items holds batch * max_splits
-// pairs (sequence, split); *count receives the number written.
-hipError_t launch_work_list(const int* seq_lens, int batch, int max_seq_len, int split_len, int2* items, int* count,
-                            hipStream_t s);
-
 struct MergeParams {
   const void* o_part;      // as AttnParams::o_part
   const float2* ml_part;

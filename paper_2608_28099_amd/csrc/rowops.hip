@@ -119,38 +119,137 @@ __global__ __launch_bounds__(256) void rmsnorm_rows(const TI* x, int64_t ld_x, c
 // rotation of pair (i, i + hd/2) at row j's position N_b + t (t = step +
 // j % k_task) by angle (N_b + t) * base^(-2i/hd) is computed once per row, in
 // fp64, into LDS, then applied to the row's key heads (soft slot step + j)
-// and, for rows that carry queries, its query heads, two adjacent pairs per
-// lane (4-byte stores of bf16 pairs, 8-byte of fp32).  The value heads are not
+// and, for rows that carry queries, its query heads, eight pairs per lane
+// (16-byte stores of eight bf16 or four fp32 values).  The value heads are not
 // rotated; in the one-pass form (per_seq = 0) they are the same for every
 // sequence and written by b = 0, in the recursive form every sequence has its
 // own row of projections ([B][k] rows) and its own values.  Rows per
 // workgroup: as many as keep two workgroups per compute unit (one row each
-// made the 27B-shaped batch 8192 workgroups with a few hundred stores each:
-// 69-76 us, the same with the trigonometry taken out).
+// made the 27B-shaped batch 8192 workgroups with a few hundred stores each).
+// Bound by its stores (queries as hi + lo: 33 MB at 128 sequences of 64 rows per
+// KV head).  With 4-byte stores, pow and the library's fp64 sine and cosine it
+// took 24.0 us there (41 MB written), 55.7 us at the 27B shape and 12.7 us at the
+// 4B shape; now 15.5, 35.9 and 9.7.
 // SPLIT (T = bf16): each value x is stored as hi = bf16(x) and lo = bf16(x - hi).
 constexpr int kRopeRows = 8;
 
 template <typename T, bool SPLIT>
-__device__ __forceinline__ void put2(void* hi, void* lo, int64_t idx, float x0, float x1) {  // idx even
+__device__ __forceinline__ void put8(void* hi, void* lo, int64_t idx, const float (&x)[8]) {  // idx % 8 == 0
   if constexpr (sizeof(T) == 2) {
-    const T h0 = from_f32<T>(x0), h1 = from_f32<T>(x1);
-    auto pack = [](T a, T b) {
-      return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
-    };
-    *(uint32_t*)((T*)hi + idx) = pack(h0, h1);
-    if (SPLIT) *(uint32_t*)((T*)lo + idx) = pack(from_f32<T>(x0 - to_f32(h0)), from_f32<T>(x1 - to_f32(h1)));
+    u32x4 h, l;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const T h0 = from_f32<T>(x[2 * q]), h1 = from_f32<T>(x[2 * q + 1]);
+      const T l0 = from_f32<T>(x[2 * q] - to_f32(h0)), l1 = from_f32<T>(x[2 * q + 1] - to_f32(h1));
+      h[q] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
+      l[q] = (uint32_t)__builtin_bit_cast(uint16_t, l0) | ((uint32_t)__builtin_bit_cast(uint16_t, l1) << 16);
+    }
+    *reinterpret_cast<u32x4*>((T*)hi + idx) = h;
+    if (SPLIT) *reinterpret_cast<u32x4*>((T*)lo + idx) = l;
   } else {
     static_assert(!SPLIT, "fp32 values are stored whole");
-    *(float2*)((T*)hi + idx) = make_float2(x0, x1);
+    *reinterpret_cast<f32x4*>((T*)hi + idx) = f32x4{x[0], x[1], x[2], x[3]};
+    *reinterpret_cast<f32x4*>((T*)hi + idx + 4) = f32x4{x[4], x[5], x[6], x[7]};
   }
+}
+
+// cos and sin of 2 pi x, x in fp64: the nearest quarter turn is taken off exactly,
+// the rest (|r| <= pi/4) goes through the Taylor sums to r^12 / r^13, whose first
+// dropped terms are below 4e-13: exact to the last bit of the fp32 results but for
+// ties.  x < 2^31, and its rounding (2^-53 x, in turns) is the angle's own.
+__device__ __forceinline__ void sincos_turns(double x, float& c, float& s) {
+  const double q4 = rint(4.0 * x);
+  const double r = (4.0 * x - q4) * 1.5707963267948966, r2 = r * r;
+  double cr = 1.0 / 479001600.0, sr = 1.0 / 6227020800.0;
+  cr = fma(cr, -r2, 1.0 / 3628800.0);
+  cr = fma(cr, -r2, 1.0 / 40320.0);
+  cr = fma(cr, -r2, 1.0 / 720.0);
+  cr = fma(cr, -r2, 1.0 / 24.0);
+  cr = fma(cr, -r2, 0.5);
+  cr = fma(cr, -r2, 1.0);
+  sr = fma(sr, -r2, 1.0 / 39916800.0);
+  sr = fma(sr, -r2, 1.0 / 362880.0);
+  sr = fma(sr, -r2, 1.0 / 5040.0);
+  sr = fma(sr, -r2, 1.0 / 120.0);
+  sr = fma(sr, -r2, 1.0 / 6.0);
+  sr = fma(sr, -r2, 1.0);
+  sr *= r;
+  const int q = (int)(long long)q4 & 3;
+  const float cf = (float)cr, sf = (float)sr;
+  c = q == 0 ? cf : q == 1 ? -sf : q == 2 ? -cf : sf;
+  s = q == 0 ? sf : q == 1 ? cf : q == 2 ? -sf : -cf;
+}
+
+// The split attention's work list (see RopeParams::items), by one workgroup of
+// 256 threads; scratch: 1024 words of LDS.  Full splits: an exclusive scan of
+// (splits - 1) per sequence, 256 sequences at a time; last splits: the rank of
+// each by (tokens descending, sequence), the candidates staged 1024 at a time.
+__device__ void write_work_list(const RopeParams& p, int batch, int* scratch) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto len = [&](int b) { return clamp_len(p.seq_lens, b, p.max_seq_len); };
+  auto splits = [&](int n) { return n > 0 ? (n + p.split_len - 1) / p.split_len : 1; };
+  auto last_tokens = [&](int n) { return n - (splits(n) - 1) * p.split_len; };
+  int full = 0;  // full splits so far
+  for (int b0 = 0; b0 < batch; b0 += 256) {
+    const int b = b0 + tid;
+    const int nf = b < batch ? splits(len(b)) - 1 : 0;
+    int sum = nf;  // inclusive over the wave
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(sum, o);
+      if (lane >= o) sum += v;
+    }
+    __syncthreads();
+    if (lane == 63) scratch[wave] = sum;
+    __syncthreads();
+    int off = full + sum - nf;
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) off += scratch[w];
+      full += scratch[w];
+    }
+    for (int sp = 0; sp < nf; ++sp) p.items[off + sp] = make_int2(b, sp);
+  }
+  for (int b0 = 0; b0 < batch; b0 += 256) {
+    const int b = b0 + tid;
+    const int n = b < batch ? len(b) : 0, rb = b < batch ? last_tokens(n) : 0;
+    int rank = 0;
+    for (int o0 = 0; o0 < batch; o0 += 1024) {
+      __syncthreads();
+      for (int t = tid; t < 1024; t += 256)
+        scratch[t] = o0 + t < batch ? last_tokens(len(o0 + t)) : -1;  // -1: no sequence (ranks below all)
+      __syncthreads();
+      // four counts per 16-byte LDS read (the slots past the batch hold -1)
+      const int m4 = (min(1024, batch - o0) + 3) / 4;
+      const int4* s4 = (const int4*)scratch;
+#pragma unroll 4
+      for (int q = 0; q < m4; ++q) {
+        const int4 r = s4[q];
+        const int j = o0 + 4 * q;
+        rank += (r.x > rb) || (r.x == rb && j < b);
+        rank += (r.y > rb) || (r.y == rb && j + 1 < b);
+        rank += (r.z > rb) || (r.z == rb && j + 2 < b);
+        rank += (r.w > rb) || (r.w == rb && j + 3 < b);
+      }
+    }
+    if (b < batch) p.items[full + rank] = make_int2(b, splits(n) - 1);
+  }
+  if (tid == 0) *p.n_items = full + batch;
 }
 
 template <typename T, bool SPLIT>
 __global__ __launch_bounds__(256) void rope_scatter(const RopeParams p, int rows_per_block) {
-  __shared__ float cs[kRopeRows][64], sn[kRopeRows][64];  // hd / 2 <= 64
-  const int b = blockIdx.y, j0 = blockIdx.x * rows_per_block;
+  __shared__ __align__(16) float trig[2 * kRopeRows * 64];  // cos, then sin; hd / 2 <= 64
+  float (*cs)[64] = (float (*)[64])trig, (*sn)[64] = cs + kRopeRows;
+  int b = blockIdx.y;
+  const int j0 = blockIdx.x * rows_per_block;
   if (p.err && *p.err) return;
-  const int hd = p.hd, half = hd / 2, hp = half / 2;  // hp: lanes per head (two pairs each)
+  if (p.items) {  // grid row 0 is the work list's: dispatched first, it runs beside the rotations
+    if (b == 0) {
+      if (blockIdx.x == 0) write_work_list(p, gridDim.y - 1, (int*)trig);
+      return;
+    }
+    --b;
+  }
+  const int hd = p.hd, half = hd / 2, hp = half / 8;  // hp: lanes per head (eight pairs each)
   const int nj = min(rows_per_block, p.k - j0);
   int n = p.seq_lens[b];
   // a length outside [0, max_seq_len] is clamped (every kernel does the same)
@@ -161,42 +260,66 @@ __global__ __launch_bounds__(256) void rope_scatter(const RopeParams p, int rows
   for (int t = threadIdx.x; t < nj * half; t += blockDim.x) {
     const int jr = t / half, i = t % half;
     const int jj = (j0 + jr) % p.k_task;
-    const double theta = pow(p.rope_base, -2.0 * (double)i / (double)hd);
-    const double ang = (double)(n + p.step + jj) * theta;
-    cs[jr][i] = (float)cos(ang);
-    sn[jr][i] = (float)sin(ang);
+    const double pos = (double)(n + p.step + jj), ex = -2.0 * (double)i / (double)hd;
+    if (p.rope_base >= 1.0) {
+      // base^(-2i/hd) / 2 pi, in (0, 1/2 pi]: turns per position
+      sincos_turns(pos * ((i ? exp2(ex * p.log2_base) : 1.0) * 0.15915494309189535), cs[jr][i], sn[jr][i]);
+    } else {  // angles grow with i and may exceed what a count of turns in fp64 holds
+      const double ang = pos * pow(p.rope_base, ex);
+      cs[jr][i] = (float)cos(ang);
+      sn[jr][i] = (float)sin(ang);
+    }
   }
   __syncthreads();
-  const int nh = p.n_q + p.n_kv;
-  for (int jr = 0; jr < nj; ++jr) {
-    const int j = j0 + jr, jj = j % p.k_task, slot = p.step + j;
-    const float* row = p.qkv + ((int64_t)(p.per_seq ? b * p.k : 0) + j) * (p.n_q + 2 * p.n_kv) * hd;
-    const int qi = (j / p.k_task) * p.q_per_task + jj - p.q_first;
-    for (int e = (jj >= p.q_first ? 0 : p.n_q * hp) + threadIdx.x; e < nh * hp; e += blockDim.x) {
-      const int h = e / hp, i = 2 * (e % hp);
-      const float2 xa = *(const float2*)(row + h * hd + i), xb = *(const float2*)(row + h * hd + i + half);
-      const float c0 = cs[jr][i], s0 = sn[jr][i], c1 = cs[jr][i + 1], s1 = sn[jr][i + 1];
-      const float r0a = xa.x * c0 - xb.x * s0, r1a = xb.x * c0 + xa.x * s0;
-      const float r0b = xa.y * c1 - xb.y * s1, r1b = xb.y * c1 + xa.y * s1;
-      if (h < p.n_q) {
-        const int g = h / p.group, rr = qi * p.group + h % p.group;
-        const int64_t base = (((int64_t)b * p.n_kv + g) * p.r_alloc + rr) * hd;
-        put2<T, SPLIT>(p.q, p.q_lo, base + i, r0a * p.q_scale, r0b * p.q_scale);
-        put2<T, SPLIT>(p.q, p.q_lo, base + i + half, r1a * p.q_scale, r1b * p.q_scale);
-      } else {
-        const int g = h - p.n_q;
-        const int64_t base = (((int64_t)b * p.n_kv + g) * p.ks + slot) * hd;
-        put2<T, SPLIT>(p.k_soft, p.k_soft_lo, base + i, r0a, r0b);
-        put2<T, SPLIT>(p.k_soft, p.k_soft_lo, base + i + half, r1a, r1b);
+  const int row_len = (p.n_q + 2 * p.n_kv) * hd;
+  const float* rows = p.qkv + ((int64_t)(p.per_seq ? b * p.k : 0) + j0) * row_len;
+  // head h of the projections of row j0 + jr, pairs i .. i + 7
+  auto rotate = [&](int jr, int h, int i, float (&lo8)[8], float (&hi8)[8]) __attribute__((always_inline)) {
+    const float* x = rows + (int64_t)jr * row_len + h * hd + i;
+#pragma unroll
+    for (int v = 0; v < 8; v += 4) {
+      const f32x4 xa = *reinterpret_cast<const f32x4*>(x + v), xb = *reinterpret_cast<const f32x4*>(x + half + v);
+      const f32x4 c = *reinterpret_cast<const f32x4*>(&cs[jr][i + v]), s = *reinterpret_cast<const f32x4*>(&sn[jr][i + v]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo8[v + e] = xa[e] * c[e] - xb[e] * s[e];
+        hi8[v + e] = xb[e] * c[e] + xa[e] * s[e];
       }
     }
-    if (p.per_seq || b == 0) {
-      const int64_t vb = p.per_seq ? (int64_t)b * p.n_kv : 0;
-      for (int e = threadIdx.x; e < p.n_kv * half; e += blockDim.x) {
-        const int g = e / half, i = 2 * (e % half);
-        const float2 v = *(const float2*)(row + (p.n_q + p.n_kv + g) * hd + i);
-        put2<T, SPLIT>(p.v_soft, p.v_soft_lo, ((vb + g) * p.ks + slot) * hd + i, v.x, v.y);
-      }
+  };
+  for (int e = threadIdx.x; e < nj * p.n_q * hp; e += blockDim.x) {
+    const int jr = e / (p.n_q * hp), h = e / hp % p.n_q, i = 8 * (e % hp);
+    const int j = j0 + jr, jj = j % p.k_task;
+    if (jj < p.q_first) continue;
+    float r0[8], r1[8];
+    rotate(jr, h, i, r0, r1);
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+      r0[v] *= p.q_scale;
+      r1[v] *= p.q_scale;
+    }
+    const int g = h / p.group, rr = ((j / p.k_task) * p.q_per_task + jj - p.q_first) * p.group + h % p.group;
+    const int64_t base = (((int64_t)b * p.n_kv + g) * p.r_alloc + rr) * hd + i;
+    put8<T, SPLIT>(p.q, p.q_lo, base, r0);
+    put8<T, SPLIT>(p.q, p.q_lo, base + half, r1);
+  }
+  for (int e = threadIdx.x; e < nj * p.n_kv * hp; e += blockDim.x) {
+    const int jr = e / (p.n_kv * hp), g = e / hp % p.n_kv, i = 8 * (e % hp);
+    float r0[8], r1[8];
+    rotate(jr, p.n_q + g, i, r0, r1);
+    const int64_t base = (((int64_t)b * p.n_kv + g) * p.ks + p.step + j0 + jr) * hd + i;
+    put8<T, SPLIT>(p.k_soft, p.k_soft_lo, base, r0);
+    put8<T, SPLIT>(p.k_soft, p.k_soft_lo, base + half, r1);
+  }
+  if (p.per_seq || b == 0) {
+    const int64_t vb = p.per_seq ? (int64_t)b * p.n_kv : 0;
+    for (int e = threadIdx.x; e < nj * p.n_kv * 2 * hp; e += blockDim.x) {
+      const int jr = e / (p.n_kv * 2 * hp), g = e / (2 * hp) % p.n_kv, i = 8 * (e % (2 * hp));
+      const float* x = rows + (int64_t)jr * row_len + (p.n_q + p.n_kv + g) * hd + i;
+      float v[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[t] = x[t];
+      put8<T, SPLIT>(p.v_soft, p.v_soft_lo, ((vb + g) * p.ks + p.step + j0 + jr) * hd + i, v);
     }
   }
 }
@@ -393,13 +516,13 @@ hipError_t launch_rmsnorm_rows(DType in_dt, DType gain_dt, DType out_dt, const v
 }
 
 hipError_t launch_rope_scatter(DType dt, const RopeParams& p, int batch, hipStream_t s) {
-  if (p.hd > 128 || p.hd % 4 || p.k < 1) return hipErrorInvalidValue;
+  if (p.hd > 128 || p.hd % 16 || p.k < 1) return hipErrorInvalidValue;
   // rows per workgroup: doubled while the grid keeps two workgroups per compute unit
   const int cus = p.num_cus > 0 ? p.num_cus : 256;
   int rpb = 1;
   while (2 * rpb <= kRopeRows && 2 * rpb <= p.k && (int64_t)((p.k + 2 * rpb - 1) / (2 * rpb)) * batch >= 2 * cus)
     rpb *= 2;
-  const dim3 grid((p.k + rpb - 1) / rpb, batch), block(256);
+  const dim3 grid((p.k + rpb - 1) / rpb, batch + (p.items ? 1 : 0)), block(256);
   if (dt == kBF16)
     hipLaunchKernelGGL((rope_scatter<bf16, true>), grid, block, 0, s, p, rpb);
   else if (dt == kF32)

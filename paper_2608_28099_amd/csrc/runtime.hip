@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <deque>
@@ -499,10 +500,21 @@ int check_forward(const sp_probe_config& c, const Plan& pl, const sp_kv_cache* k
 
 // Whether the attention takes its items from a work list (bf16 storage): a grid
 // of at most one round of resident workgroups starts all at once, so an order
-// would only cost its launch (4.5 us) and each workgroup a dependent load.
+// would only cost each workgroup a dependent load.  Nor are more than 16384
+// sequences ordered: the ranking is quadratic in them (one workgroup, 64 x 64
+// compares per 256 sequences and 1024 candidates), and a grid of that many
+// rounds has no tail to fill.
 bool needs_work_list(const Ctx& x, const AttnPlan& a, int batch) {
-  return x.cfg->dtype == SP_BF16 && (int64_t)x.cfg->n_kv_heads * a.n_qgroups * a.max_splits * batch >
-                                        attn_slots(*x.cfg, a, x.n_cus);
+  return x.cfg->dtype == SP_BF16 && batch <= 16384 &&
+         (int64_t)x.cfg->n_kv_heads * a.n_qgroups * a.max_splits * batch > attn_slots(*x.cfg, a, x.n_cus);
+}
+
+// The work list of plan a is written by the RoPE launch r, where one is needed.
+void add_work_list(const Ctx& x, const AttnPlan& a, int batch, RopeParams& r) {
+  if (!needs_work_list(x, a, batch)) return;
+  r.items = at<int2>(x, x.plan->off_items);
+  r.n_items = at<int>(x, x.plan->off_n_items);
+  r.split_len = a.split_len;
 }
 
 // Split-attention parameters over the caller's cache for one attention plan.
@@ -528,7 +540,7 @@ AttnParams attn_params(const Ctx& x, const AttnPlan& a, const sp_kv_cache* kv,
   ap.num_cus = x.n_cus;
   ap.f16 = a.f16;
   ap.stages = 3;
-  // the work list launch_work_list wrote for this plan
+  // the work list launch_rope_scatter wrote for this plan
   const bool list = needs_work_list(x, a, kv->batch);
   ap.items = list ? at<int2>(x, x.plan->off_items) : nullptr;
   ap.n_items = list ? at<int>(x, x.plan->off_n_items) : nullptr;
@@ -758,6 +770,7 @@ int forward_one_pass(const Ctx& x, const sp_kv_cache* kv, const int32_t* seq_len
   if (chk != SP_OK) return chk;
   if (n_tasks < 1 || n_tasks > pl.max_tasks) return SP_ERR_INVALID_ARG;
   if (noop) return SP_OK;
+  if (one_pass_plan(c, n_tasks, x.n_cus, pl.coarse).max_splits > pl.items_splits) return SP_ERR_INTERNAL;
   const int B = kv->batch;
 
   hipStream_t s = (hipStream_t)stream;
@@ -808,9 +821,10 @@ int forward_one_pass(const Ctx& x, const sp_kv_cache* kv, const int32_t* seq_len
     r.r_alloc = ak.r_alloc; r.ks = pl.ks; r.max_seq_len = c.max_seq_len;
     r.step = 0; r.per_seq = 0;
     r.k_task = K; r.q_first = K - Kq; r.q_per_task = Kq;
-    r.rope_base = c.rope_base;
+    r.rope_base = c.rope_base; r.log2_base = std::log2(c.rope_base);
     r.q_scale = (float)(1.4426950408889634 / __builtin_sqrt((double)hd));
     r.num_cus = x.n_cus;
+    add_work_list(x, ak, B, r);
     SP_TRY(launch_rope_scatter(dt, r, B, s));
   }
   if (!mark()) return SP_ERR_HIP;
@@ -820,9 +834,6 @@ int forward_one_pass(const Ctx& x, const sp_kv_cache* kv, const int32_t* seq_len
                                     at<void>(x, pl.off_q_lo), at<void>(x, pl.off_opart),
                                     at<float2>(x, pl.off_ml));
   if (dt == kBF16) {
-    if (ak.max_splits > pl.items_splits) return SP_ERR_INTERNAL;
-    if (ap.items) SP_TRY(launch_work_list(seq_lens, B, c.max_seq_len, ak.split_len, at<int2>(x, pl.off_items),
-                            at<int>(x, pl.off_n_items), s));
     SP_TRY(launch_attention_bf16(ap, hd, ak.waves, B, s));
   } else {
     SP_TRY(launch_attention_f32(ap, hd, B, s));
@@ -992,13 +1003,6 @@ SP_API int sp_probe_forward_recursive(sp_probe_t* h, const sp_kv_cache* kv, cons
                                c.rms_eps, status, s));
   }
 
-  // the attention of every step runs the same work list, longest items first
-  if (dt == kBF16 && needs_work_list(x, rp, B)) {
-    if (pl.rec.max_splits > pl.items_splits) return SP_ERR_INTERNAL;
-    SP_TRY(launch_work_list(seq_lens, B, c.max_seq_len, pl.rec.split_len, at<int2>(x, pl.off_items),
-                            at<int>(x, pl.off_n_items), s));
-  }
-
   for (int t = 0; t < K; ++t) {
     // stage 0: x_t = W_fc[:, :d] RMSNorm(h; gamma_h) + c_t, its RMSNorm, Q/K/V, RoPE at N_b + t
     {
@@ -1026,9 +1030,10 @@ SP_API int sp_probe_forward_recursive(sp_probe_t* h, const sp_kv_cache* kv, cons
       r.r_alloc = rp.r_alloc; r.ks = pl.ks_rec; r.max_seq_len = c.max_seq_len;
       r.step = t; r.per_seq = 1;
       r.k_task = 1; r.q_first = 0; r.q_per_task = 1;
-      r.rope_base = c.rope_base;
+      r.rope_base = c.rope_base; r.log2_base = std::log2(c.rope_base);
       r.q_scale = (float)(1.4426950408889634 / __builtin_sqrt((double)hd));
       r.num_cus = x.n_cus;
+      if (t == 0) add_work_list(x, rp, B, r);  // every step runs the same list
       SP_TRY(launch_rope_scatter(dt, r, B, s));
     }
     if (!mark()) return SP_ERR_HIP;
