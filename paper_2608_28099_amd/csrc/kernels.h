@@ -58,6 +58,10 @@ struct RopeParams {
   int2* items;
   int* n_items;
   int split_len;
+  // also write zeros to the padding: query rows past the launch's own up to
+  // r_alloc, key and value slots past step + k up to ks (a workspace that holds
+  // other contents; a handle's padding is zero from its start)
+  int clear_padding;
 };
 // dt: output type: kF32, or kBF16 for the hi/lo bf16 split
 hipError_t launch_rope_scatter(DType dt, const RopeParams& p, int batch, hipStream_t s);

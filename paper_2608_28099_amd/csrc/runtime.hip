@@ -377,9 +377,10 @@ struct Ctx {
   char* ws;
   int n_cus, n_xcd;
   sp_probe* prof;
+  bool stale;  // the workspace holds another call's contents (its padding is not zero)
 };
 
-Ctx ctx_of(sp_probe* h) { return Ctx{&h->cfg, &h->plan, h->ws, h->num_cus, h->n_xcd, h}; }
+Ctx ctx_of(sp_probe* h) { return Ctx{&h->cfg, &h->plan, h->ws, h->num_cus, h->n_xcd, h, false}; }
 
 template <typename T>
 T* at(const Ctx& x, size_t off) { return reinterpret_cast<T*>(x.ws + off); }
@@ -824,6 +825,7 @@ int forward_one_pass(const Ctx& x, const sp_kv_cache* kv, const int32_t* seq_len
     r.rope_base = c.rope_base; r.log2_base = std::log2(c.rope_base);
     r.q_scale = (float)(1.4426950408889634 / __builtin_sqrt((double)hd));
     r.num_cus = x.n_cus;
+    r.clear_padding = x.stale;
     add_work_list(x, ak, B, r);
     SP_TRY(launch_rope_scatter(dt, r, B, s));
   }
@@ -1246,22 +1248,9 @@ SP_API int sp_probe_forward_noalloc(const sp_probe_config* cfg, const sp_kv_cach
   if (sd.status != SP_OK) return sd.status;
   const Plan pl = make_plan(*cfg, sd.num_cus);
   if (pl.total > kScratchBytes) return SP_ERR_CAPACITY;
-  const Ctx x{cfg, &pl, sd.ptr, sd.num_cus, sd.n_xcd, nullptr};
-  // host checks first: on error nothing is enqueued
-  bool noop = false;
-  st = check_forward(*cfg, pl, kv, seq_lens, block_table, soft_prompt, weights, logits, &noop);
-  if (st != SP_OK || noop) return st;
-  // The array keeps the last call's contents (possibly of another config):
-  // clear what a forward expects to start at zero, the padded query rows and
-  // soft key/value slots and the flag words, with a fill kernel.
-  hipStream_t s = (hipStream_t)stream;
-  const size_t zero_from[] = {pl.off_q, pl.off_ksoft, pl.off_vsoft, pl.off_q_lo, pl.off_ksoft_lo,
-                              pl.off_vsoft_lo, pl.off_err};
-  const size_t zero_to[] = {pl.off_ksoft, pl.off_vsoft, pl.off_q_lo, pl.off_ksoft_lo, pl.off_vsoft_lo,
-                            pl.off_opart, pl.off_err + 256};
-  for (int i = 0; i < 7; ++i)
-    if (zero_to[i] > zero_from[i] &&
-        launch_fill_words((uint32_t*)(sd.ptr + zero_from[i]), (zero_to[i] - zero_from[i]) / 4, 0u, s) != hipSuccess)
-      return SP_ERR_HIP;
+  const Ctx x{cfg, &pl, sd.ptr, sd.num_cus, sd.n_xcd, nullptr, true};
+  // The array keeps the last call's contents, possibly of another config; the
+  // forward clears its padding itself (stale), and the flag words, which no one
+  // reads without a handle, keep what they hold.
   return forward_one_pass(x, kv, seq_lens, block_table, 1, soft_prompt, weights, logits, stream);
 }
