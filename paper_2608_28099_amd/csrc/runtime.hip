@@ -499,15 +499,18 @@ int check_forward(const sp_probe_config& c, const Plan& pl, const sp_kv_cache* k
   return SP_OK;
 }
 
-// Whether the attention takes its items from a work list (bf16 storage): a grid
-// of at most one round of resident workgroups starts all at once, so an order
-// would only cost each workgroup a dependent load.  Nor are more than 16384
-// sequences ordered: the ranking is quadratic in them (one workgroup, 64 x 64
-// compares per 256 sequences and 1024 candidates), and a grid of that many
-// rounds has no tail to fill.
+// Whether the attention takes its items from a work list (bf16 storage).  Not a
+// single sequence, whose splits are alike, nor whole sequences that all start at
+// once: an order would only cost each workgroup a dependent load.  A ragged batch
+// of one round needs it as much as a longer grid: without it the slots past its
+// short sequences' ends fall on some compute units and spare others (8 sequences
+// of 7451-59610 tokens: 353 us per forward with the list, 408 without).  Nor are
+// more than 16384 sequences ordered: the ranking is quadratic in them (one
+// workgroup beside the rotations), and a grid of that many rounds has no tail to
+// fill.
 bool needs_work_list(const Ctx& x, const AttnPlan& a, int batch) {
-  return x.cfg->dtype == SP_BF16 && batch <= 16384 &&
-         (int64_t)x.cfg->n_kv_heads * a.n_qgroups * a.max_splits * batch > attn_slots(*x.cfg, a, x.n_cus);
+  if (x.cfg->dtype != SP_BF16 || batch == 1 || batch > 16384) return false;
+  return a.max_splits > 1 || (int64_t)x.cfg->n_kv_heads * a.n_qgroups * batch > attn_slots(*x.cfg, a, x.n_cus);
 }
 
 // The work list of plan a is written by the RoPE launch r, where one is needed.
