@@ -214,9 +214,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
 }
 
 // ---------------------------------------------------------------- few rows
-// C = A W^T on at most 16 rows: bound by the read of the weights, so the kernel
-// is a reader of W with matrix-core products.  One workgroup takes 16 weight rows
-// (SwiGLU: 16 gate rows and the 16 matching up rows) over the whole of K; its NW
+// C = A W^T on at most 16 rows (or few 16-row tiles of small matrices, one per
+// blockIdx.y): bound by the read of the weights, so the kernel is a reader of W
+// with matrix-core products.  One workgroup takes 16 weight rows (SwiGLU: 16
+// gate rows and the 16 matching up rows) over the whole of K; its NW
 // waves take contiguous slices of K, load their A and W fragments straight into
 // registers (16 bytes per lane; no wave shares a fragment with another, so LDS
 // would only add a copy) U steps of 32 ahead, and the partial tiles are summed in
@@ -227,7 +228,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
 // 30.6 -> 21.5 us (4.7 TB/s, launch included), 2560 x 9728 22.7 -> 16.6 us, SwiGLU
 // 24576 x 4096 53.5 -> 38.9 us (5.2 TB/s); 16 rows, SwiGLU 54.3 -> 45.2 us.  What
 // is left over the read is the A fragments, which every workgroup fetches from
-// its L2: 1 row takes 2-3 us less than 8.
+// its L2: 1 row takes 2-3 us less than 8.  Several row tiles: 20 rows of 512 x 768
+// 10.0 us as four 32 x 128 tiles, 5.6 us here.
 // PK = 2 (at most 8 rows): a 16-row A fragment would be half repeats, so one load
 // brings two steps of the 8 rows (lanes li 0-7 the even step, 8-15 the odd one)
 // and the odd step's product takes the fragment rotated by 8 rows; rows 8-15 of
@@ -251,8 +253,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows(const GemmParams p) {
   const int KT = p.K / 32, KP = (KT + 1) / 2;  // steps of 32; pairs of steps (whole 128-byte lines of W)
   const int kb = 2 * (KP * wave / NW), ke = min(KT, 2 * (KP * (wave + 1) / NW));
 
+  const int m0 = 16 * blockIdx.y;
   // rows past M read row M - 1 again; never stored
-  const uint16_t* ap = (const uint16_t*)p.a + (int64_t)min(li % RP, p.M - 1) * p.lda + 8 * la;
+  const uint16_t* ap = (const uint16_t*)p.a + (int64_t)min(m0 + li % RP, p.M - 1) * p.lda + 8 * la;
   const uint16_t* wp[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -303,7 +306,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows(const GemmParams p) {
   for (int j = 0; j < NT; ++j) red[wave][j][lane] = acc[j];
   __syncthreads();
   if (wave > 0) return;
-  // lane holds C[4la + r][16 blockIdx.x + li]
+  // lane holds C[m0 + 4la + r][16 blockIdx.x + li]
   f32x4 v[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows(const GemmParams p) {
   const int n = 16 * blockIdx.x + li;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int m = 4 * la + r;
+    const int m = m0 + 4 * la + r;
     if (m >= p.M) continue;
     if (EPI == kEpiSwiglu) {
       const float s = silu(v[0][r]) * v[NT - 1][r];
@@ -337,9 +340,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows(const GemmParams p) {
 template <int NW, int U, int PK, int EPI>
 hipError_t launch_rows(const GemmParams& p, hipStream_t s) {
   constexpr int cols = EPI == kEpiSwiglu ? 32 : 16;
-  if (p.M < 1 || p.M > 16 / PK || p.K % 32 || p.N % cols) return hipErrorInvalidValue;
+  if (p.M < 1 || (PK == 2 && p.M > 8) || p.K % 32 || p.N % cols) return hipErrorInvalidValue;
   if (EPI != kEpiSwiglu && (p.b_split0 % 16 || p.b_split1 % 16)) return hipErrorInvalidValue;
-  const dim3 block(64 * NW), grid(p.N / cols);
+  const dim3 block(64 * NW), grid(p.N / cols, (p.M + 15) / 16);
   if (p.b_f16) hipLaunchKernelGGL((gemm_rows<NW, U, PK, EPI, false>), grid, block, 0, s, p);
   else hipLaunchKernelGGL((gemm_rows<NW, U, PK, EPI, true>), grid, block, 0, s, p);
   return hipGetLastError();
@@ -743,12 +746,13 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // tiles (8 row tiles by 4 column tiles with 32 compute units per XCD)
   if (p.group_m < 1) p.group_m = 8;
   auto fits = [&](int ks) { return p.part && (size_t)ks * p.M * p.N * sizeof(float) <= p.part_bytes; };
-  // Up to 16 rows: SwiGLU, and the other products with at most one 16-column
-  // tile per compute unit, on gemm_rows.  Wider products keep the one-wave tiles
-  // below: their tiles do not divide evenly over the compute units either way,
-  // and one wave each balances better (5 rows: 6144 x 4096 12.5 us against 13.5,
-  // 5120 x 17408 42.0 us against 47.9).
-  if (p.M <= 16 && (epi == kEpiSwiglu || p.N / 16 <= cus) && p.N % (epi == kEpiSwiglu ? 32 : 16) == 0 &&
+  // gemm_rows: at most one workgroup per compute unit (16 rows of matrices up to
+  // 4096 wide, more rows of narrower ones), and SwiGLU on up to 16 rows.  Wider
+  // products on few rows keep the one-wave tiles below: their tiles do not divide
+  // evenly over the compute units either way, and one wave each balances better
+  // (5 rows: 6144 x 4096 12.5 us against 13.5, 5120 x 17408 42.0 us against 47.9).
+  const int rows_cols = epi == kEpiSwiglu ? 32 : 16;
+  if (((epi == kEpiSwiglu && p.M <= 16) || (int64_t)(p.N / rows_cols) * ((p.M + 15) / 16) <= cus) && p.N % rows_cols == 0 &&
       (epi == kEpiSwiglu || (p.b_split0 % 16 == 0 && p.b_split1 % 16 == 0)))
     return launch_gemm_rows(epi, p, s);
   // 17..32 rows: the product streams the weights; a 32-row by 128-column tile

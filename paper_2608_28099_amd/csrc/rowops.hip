@@ -397,7 +397,7 @@ __global__ __launch_bounds__(256) void final_classifier(const ClsParams p) {
 // One workgroup per row: max |x| over the row, then the scaled fp16 copy, eight
 // values per load (cols % 8 == 0, rows 16-byte aligned).  Bound by two passes of
 // load latency: 2-byte loads and a counted exponent took 14.2 us for 9 rows of
-// 7680, this SCALE_AFTER us.
+// 7680, this 3.0 us.
 __global__ __launch_bounds__(1024) void scale_rows_f16(const bf16* x, int64_t ld_x, f16* out,
                                                        float* inv_scale, int cols) {
   __shared__ float red[16];
