@@ -325,8 +325,9 @@ int sp_probe_check_device_error(sp_probe_t* h, void* stream);
  * read (waits for them).  Stages, in order: 0 soft-row prep (norm, QKV, RoPE;
  * recursive: with the fusion), 1 split attention, 2 split merge, 3 o-projection,
  * 4 post-attention norm, 5 gate/up + SwiGLU, 6 down projection, 7 final norm +
- * classifier (recursive: the final norm of every step); a recursive forward adds
- * its k steps into the same stages.  stage_ms[n_stages] receives milliseconds,
+ * classifier (recursive: the final norm of every step); a norm that follows a
+ * projection whose K is split runs in its reduction and counts with the
+ * projection; a recursive forward adds its k steps into the same stages.  stage_ms[n_stages] receives milliseconds,
  * *n_forwards the number of forwards counted: the last ones whose events fit a
  * pool of 256 * (SP_N_STAGES + 1) (256 one-pass forwards; 2304 / (8k + 1)
  * recursive ones). */

@@ -562,6 +562,114 @@ __global__ __launch_bounds__(256) void gemm_reduce4(const GemmParams p, int kspl
   *reinterpret_cast<float4*>((float*)p.c + (int64_t)m * p.ldc + o) = v;
 }
 
+// The same sums with the row's RMSNorm (or two in a row) after them: one workgroup
+// per row, one thread per four values (CH chunks of blockDim of them), so that a
+// row's slices are all requested at once and the row stays in registers between
+// the sum and the norm.  Bound by launch and load latency: one launch less than
+// gemm_reduce4 and rmsnorm_rows (128 rows of 4096, four slices: 9.6 us for the
+// two, 6.0 us here).
+template <int EPI, int CH>
+__global__ __launch_bounds__(1024) void gemm_reduce_norm(const GemmParams p, int ksplit) {
+  __shared__ float red[2][16];
+  const int m = blockIdx.x, d = p.N, T = blockDim.x, tid = threadIdx.x;
+  const int64_t slice = (int64_t)p.M * d;
+  const float* src = p.part + (int64_t)m * d;
+  f32x4 v[CH], g[CH];
+  auto load_gain = [&](const void* gain) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int i = 4 * (tid + T * c);
+      if (i < d) {
+        const bf16x4 h = *reinterpret_cast<const bf16x4*>((const bf16*)gain + i);
+        g[c] = f32x4{(float)h[0], (float)h[1], (float)h[2], (float)h[3]};
+      }
+    }
+  };
+  auto row_sum = [&](float x, float* r) __attribute__((always_inline)) {
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    if ((tid & 63) == 0) r[tid >> 6] = x;
+    __syncthreads();
+    float s = r[0];
+    for (int w = 1; w < T / 64; ++w) s += r[w];
+    return s;
+  };
+  f32x4 res[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int i = 4 * (tid + T * c);
+    v[c] = res[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (i >= d) continue;
+    if (EPI == kEpiResidRow) {
+      const bf16x4 r = *reinterpret_cast<const bf16x4*>((const bf16*)p.r + (int64_t)(m % p.r_mod) * p.r_ld + i);
+      res[c] = f32x4{(float)r[0], (float)r[1], (float)r[2], (float)r[3]};
+    }
+    if (EPI == kEpiResidF32) res[c] = *reinterpret_cast<const f32x4*>((const float*)p.r + (int64_t)m * p.r_ld + i);
+  }
+  load_gain(p.norm_gain);
+  for (int k0 = 0; k0 < ksplit; k0 += 4) {
+    f32x4 t[4][CH];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+        if (k0 + q < ksplit && 4 * (tid + T * c) < d)
+          t[q][c] = *reinterpret_cast<const f32x4*>(src + (k0 + q) * slice + 4 * (tid + T * c));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+        if (k0 + q < ksplit && 4 * (tid + T * c) < d) v[c] += t[q][c];
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int i = 4 * (tid + T * c);
+    if (i >= d) continue;
+    v[c] += res[c];
+    *reinterpret_cast<f32x4*>((float*)p.c + (int64_t)m * p.ldc + i) = v[c];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ss += v[c][e] * v[c][e];
+  }
+  float inv = 1.0f / sqrtf(row_sum(ss, red[0]) / (float)d + p.norm_eps);
+  for (int pass = 0; pass < (p.norm_gain2 ? 2 : 1); ++pass) {
+    float ss2 = 0.f;
+    if (pass) load_gain(p.norm_gain2);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      if (4 * (tid + T * c) >= d) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[c][e] = v[c][e] * inv * g[c][e];
+        ss2 += v[c][e] * v[c][e];
+      }
+    }
+    if (p.norm_gain2 && pass == 0) inv = 1.0f / sqrtf(row_sum(ss2, red[1]) / (float)d + p.norm_eps);
+  }
+  bool oor = false;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int i = 4 * (tid + T * c);
+    if (i >= d) continue;
+    f16x4 h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      h[e] = (f16)v[c][e];
+      oor |= !(fabsf(v[c][e]) <= 65504.0f);
+    }
+    *reinterpret_cast<f16x4*>((f16*)p.norm_out + (int64_t)m * p.norm_ld + i) = h;
+  }
+  if (__any(oor) && (tid & 63) == 0 && p.status) atomicOr(p.status, kStatusRange);
+}
+
+template <int EPI>
+hipError_t launch_reduce_norm(const GemmParams& p, int ksplit, hipStream_t s) {
+  const int ch = (p.N + 4095) / 4096, t = (p.N / 4 + ch - 1) / ch;
+  const dim3 grid(p.M), block((t + 63) / 64 * 64);
+  if (ch == 1) hipLaunchKernelGGL((gemm_reduce_norm<EPI, 1>), grid, block, 0, s, p, ksplit);
+  else hipLaunchKernelGGL((gemm_reduce_norm<EPI, 2>), grid, block, 0, s, p, ksplit);
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int WGM, int WGN, int S, int BK, bool PART, bool WB>
 hipError_t launch_tile_k(Epilogue epi, const GemmParams& p, dim3 grid, hipStream_t s) {
   const dim3 block(64 * WGM * WGN);
@@ -654,6 +762,14 @@ hipError_t launch_gemm_reduce(Epilogue epi, const GemmParams& p, int ksplit, int
                    (epi == kEpiSwiglu ? ((uintptr_t)p.c & 7) == 0 && bn % 32 == 0 : al16(p.c)) &&
                    (epi == kEpiResidRow ? p.r_ld % 4 == 0 && ((uintptr_t)p.r & 7) == 0 : true) &&
                    (epi == kEpiResidF32 ? p.r_ld % 4 == 0 && al16(p.r) : true) && p.M <= 65535;
+  // the norm that follows, where one is asked for (rows of up to 8192 values)
+  if (vec && p.norm_gain && p.norm_done && p.N <= 8192 && p.norm_ld % 4 == 0 && ((uintptr_t)p.norm_out & 7) == 0 &&
+      ((uintptr_t)p.norm_gain & 7) == 0 && ((uintptr_t)p.norm_gain2 & 7) == 0) {
+    if (epi == kEpiResidRow || epi == kEpiResidF32) {
+      *p.norm_done = true;
+      return epi == kEpiResidRow ? launch_reduce_norm<kEpiResidRow>(p, ksplit, s) : launch_reduce_norm<kEpiResidF32>(p, ksplit, s);
+    }
+  }
   if (vec) {
     const dim3 g4((unsigned)((n_out / 4 + 255) / 256), (unsigned)p.M);
     switch (epi) {

@@ -166,6 +166,16 @@ struct GemmParams {
   int b_f16;               // the weight blocks are fp16 (a converted image), not bf16
   int n_cus, n_xcd;        // compute units and XCDs of the device
   int group_m;             // row tiles per group of the tile order (0: the launcher's choice)
+  // nullable (bf16 storage; residual epilogues): the RMSNorm of the product's
+  // rows that follows it, as launch_rmsnorm_rows defines it (bf16 gains, fp16
+  // output, the second gain nullable).  Where the launcher splits K, the
+  // reduction applies it and sets *norm_done; else it is left to the caller.
+  const void* norm_gain;
+  const void* norm_gain2;
+  void* norm_out;          // [M][norm_ld]
+  int64_t norm_ld;
+  float norm_eps;
+  bool* norm_done;
 };
 // dt: storage dtype of the weights (kF32: fp32 matrix-core path; kBF16: fp16 MFMA path)
 hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p, hipStream_t s);

@@ -432,6 +432,29 @@ hipError_t run_gemm(const Ctx& x, DType dt, Epilogue epi, GemmParams g, hipStrea
   return launch_gemm(dt, epi, g, s);
 }
 
+// A residual projection and the RMSNorm of its M rows of d values (fp32, row
+// stride ldc) that follows it: norm_out[m] = fp16 or fp32 activations, row stride
+// d.  `between` runs after the projection (a stage mark).
+template <typename F>
+hipError_t run_gemm_norm(const Ctx& x, DType dt, DType at_dt, Epilogue epi, GemmParams g, const void* gain,
+                         const void* gain2, void* norm_out, F between, hipStream_t s) {
+  bool done = false;
+  if (dt == kBF16) {
+    g.norm_gain = gain;
+    g.norm_gain2 = gain2;
+    g.norm_out = norm_out;
+    g.norm_ld = g.N;
+    g.norm_eps = x.cfg->rms_eps;
+    g.norm_done = &done;
+  }
+  hipError_t e = run_gemm(x, dt, epi, g, s);
+  if (e != hipSuccess) return e;
+  if (!between()) return hipErrorUnknown;
+  if (done) return hipSuccess;
+  return launch_rmsnorm_rows(kF32, dt, at_dt, g.c, g.ldc, gain, gain2, norm_out, g.N, g.M, g.N, x.cfg->rms_eps,
+                             status_word(x), s);
+}
+
 // The head's projection matrices as the GEMMs read them: the caller's
 // matrices, or the segments of an fp16 weight image (f16 = 1).
 struct ProjW {
@@ -872,13 +895,9 @@ int forward_one_pass(const Ctx& x, const sp_kv_cache* kv, const int32_t* seq_len
     g.r = (const char*)soft_prompt + (size_t)(K - Kq) * d * pl.esz;
     g.r_mod = R;
     g.r_ld = last_only ? K * d : d;
-    SP_TRY(run_gemm(x, dt, kEpiResidRow, g, s));
+    // stage 4: w = RMSNorm(a; gamma_post)
+    SP_TRY(run_gemm_norm(x, dt, at_dt, kEpiResidRow, g, wt->post_norm, nullptr, at<void>(x, pl.off_w), mark, s));
   }
-  if (!mark()) return SP_ERR_HIP;
-
-  // stage 4: w = RMSNorm(a; gamma_post)
-  SP_TRY(launch_rmsnorm_rows(kF32, dt, at_dt, at<void>(x, pl.off_a), d, wt->post_norm, nullptr,
-                             at<void>(x, pl.off_w), d, M, d, c.rms_eps, status, s));
   if (!mark()) return SP_ERR_HIP;
 
   // stage 5: s = silu(W_gate w) * (W_up w)
@@ -1014,10 +1033,8 @@ SP_API int sp_probe_forward_recursive(sp_probe_t* h, const sp_kv_cache* kv, cons
       GemmParams g = gemm_one(hn, d, fusion->w_fc, 2 * d, x_all + (size_t)t * d * 4, (int)ld_steps,
                               B, d, d);
       g.r = at<char>(x, pl.off_rce) + (size_t)t * d * 4; g.r_ld = 0;
-      SP_TRY(run_gemm(x, dt, kEpiResidF32, g, s));
+      SP_TRY(run_gemm_norm(x, dt, at_dt, kEpiResidF32, g, wt->in_norm, nullptr, at<void>(x, pl.off_ru), [] { return true; }, s));
     }
-    SP_TRY(launch_rmsnorm_rows(kF32, dt, at_dt, x_all + (size_t)t * d * 4, ld_steps, wt->in_norm,
-                               nullptr, at<void>(x, pl.off_ru), d, B, d, c.rms_eps, status, s));
     SP_TRY(run_gemm(x, dt, kEpiStore, gemm_qkv(c, pl, pw, at<void>(x, pl.off_ru), at<void>(x, pl.off_rqkv), B), s));
     {
       RopeParams r{};
@@ -1078,13 +1095,9 @@ SP_API int sp_probe_forward_recursive(sp_probe_t* h, const sp_kv_cache* kv, cons
                               a_all + (size_t)t * d * 4, (int)ld_steps, B, d, qw);
       g.b_f16 = pw.f16;
       g.r = x_all + (size_t)t * d * 4; g.r_ld = (int)ld_steps;
-      SP_TRY(run_gemm(x, dt, kEpiResidF32, g, s));
+      // stage 4: w = RMSNorm(a_t; gamma_post)
+      SP_TRY(run_gemm_norm(x, dt, at_dt, kEpiResidF32, g, wt->post_norm, nullptr, at<void>(x, pl.off_w), mark, s));
     }
-    if (!mark()) return SP_ERR_HIP;
-
-    // stage 4: w = RMSNorm(a_t; gamma_post)
-    SP_TRY(launch_rmsnorm_rows(kF32, dt, at_dt, a_all + (size_t)t * d * 4, ld_steps, wt->post_norm,
-                               nullptr, at<void>(x, pl.off_w), d, B, d, c.rms_eps, status, s));
     if (!mark()) return SP_ERR_HIP;
 
     // stage 5: s = silu(W_gate w) * (W_up w)
@@ -1097,17 +1110,17 @@ SP_API int sp_probe_forward_recursive(sp_probe_t* h, const sp_kv_cache* kv, cons
                               (int)ld_steps, B, d, I);
       g.b_f16 = pw.f16;
       g.r = a_all + (size_t)t * d * 4; g.r_ld = (int)ld_steps;
-      SP_TRY(run_gemm(x, dt, kEpiResidF32, g, s));
+      // stage 7: the step's output f_t = RMSNorm(y_t; gamma_final) is the next
+      // step's hidden state, which enters it as RMSNorm(f_t; gamma_h); after the
+      // last step, the read-out and the classifier
+      if (t + 1 < K) {
+        SP_TRY(run_gemm_norm(x, dt, at_dt, kEpiResidF32, g, wt->final_norm, fusion->fc_norm_hidden, hn, mark, s));
+      } else {
+        SP_TRY(run_gemm(x, dt, kEpiResidF32, g, s));
+        if (!mark()) return SP_ERR_HIP;
+      }
     }
-    if (!mark()) return SP_ERR_HIP;
-
-    // stage 7: the step's output f_t = RMSNorm(y_t; gamma_final) is the next
-    // step's hidden state, which enters it as RMSNorm(f_t; gamma_h); after the
-    // last step, the read-out and the classifier
-    if (t + 1 < K) {
-      SP_TRY(launch_rmsnorm_rows(kF32, dt, at_dt, y_all + (size_t)t * d * 4, ld_steps, wt->final_norm,
-                                 fusion->fc_norm_hidden, hn, d, B, d, c.rms_eps, status, s));
-    } else {
+    if (t + 1 == K) {
       ClsParams cp{};
       cp.y = (const float*)y_all;
       cp.final_norm = wt->final_norm; cp.w_cls = wt->w_cls; cp.b_cls = wt->b_cls;
