@@ -30,6 +30,14 @@
 // compact block of group_m row tiles by (CUs per XCD / group_m) column tiles,
 // instead of every row tile of one column tile, and fetch far fewer operand
 // bytes from beyond the L2 (27B-shaped gate/up on 8192 rows: 15% faster).
+// K order: on the STREAM tiles each column tile starts its slice at another step and
+// wraps round.  A product of few rows streams the weights, and workgroups in step
+// all read the same K columns, whose lines lie a row (a multiple of 8 KB) apart
+// and so crowd onto few memory channels; started apart they spread (128 rows,
+// SwiGLU 24576 x 4096 in 128 x 96 tiles: 48.1 -> 42.5 us; 90 rows 46.7 -> 40.1).
+// Products of many rows keep the common order, in which neighbours share operand
+// lines in the L2.  Column tiles need not divide N: a last tile re-reads the
+// last 32 columns in place of those past N and does not store them.
 #include "common.h"
 #include "kernels.h"
 
@@ -51,7 +59,8 @@ __device__ __forceinline__ void tile_of(int L, int nwg, int mtiles, int ntiles, 
   n_tile = in / gm;
 }
 
-template <int BM, int BN, int WGM, int WGN, int S, int BK, int EPI, bool PART, bool WBF16>
+// STREAM: the tiles of few rows, with the K order by column tile and ragged columns.
+template <int BM, int BN, int WGM, int WGN, int S, int BK, bool STREAM, int EPI, bool PART, bool WBF16>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
   constexpr int NW = WGM * WGN, WM = BM / WGM, WN = BN / WGN, MT = WM / 16, NT = WN / 16;
   constexpr int PPR = BK / 8;                        // 16-byte pieces per tile row
@@ -60,6 +69,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
   constexpr int NIA = BM / RPI, NI = NIA + BN / RPI;  // 64-piece loads per step
   constexpr int IPW = (NI + NW - 1) / NW;            // loads per wave per step
   constexpr int STAGE = (BM + BN) * PPR;             // pieces per stage
+  static_assert(!STREAM || BN % 32 == 0, "ragged columns come 32 at a time");
+  // SwiGLU on one row tile (the streaming tiles): the weights are read once, so
+  // their loads are non-temporal and leave the activations in the L2 (16 rows,
+  // 24576 x 4096: 37.3 -> 33.6 us; 128 rows: 42.5 -> 41.8; with K split it measured slower)
+  constexpr bool WNT = STREAM && EPI == kEpiSwiglu && !PART && BM <= 128;
   static_assert(BK == 32 || BK == 64, "step depth");
   static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile");
   static_assert(S >= 2 && (S - 2) * IPW < 64, "stages");
@@ -71,7 +85,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
   __builtin_assume(wave >= 0 && wave < NW);
   const int wm = wave / WGN, wn = wave % WGN;
 
-  const int mtiles = (p.M + BM - 1) / BM, ntiles = p.N / BN;
+  const int mtiles = (p.M + BM - 1) / BM, ntiles = (p.N + BN - 1) / BN;
   int m_tile, n_tile;
   tile_of(blockIdx.x, gridDim.x, mtiles, ntiles, p.n_xcd, p.group_m, m_tile, n_tile);
   const int m0 = m_tile * BM, n0 = n_tile * BN;
@@ -96,12 +110,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
       lds_piece[j] = blk * 64;
     } else {
       int src, row;
+      const int r = blk * RPI, n = STREAM ? min(n0 + (r & ~31), p.N - 32) + (r & 31) : n0 + r;
       if (EPI == kEpiSwiglu) {  // an RPI-row block lies inside one 16-row gate or up group
-        const int r = blk * RPI;
-        src = (r >> 4) & 1;
-        row = n_tile * (BN / 2) + 16 * (r >> 5) + (r & 15) + row_in;
-      } else {
-        const int n = n0 + blk * RPI;  // b_split0/1 are multiples of BN
+        src = (n >> 4) & 1;
+        row = 16 * (n >> 5) + (n & 15) + row_in;
+      } else {  // b_split0/1 are multiples of 32
         src = n < p.b_split0 ? 0 : (n < p.b_split1 ? 1 : 2);
         row = n - (src == 0 ? 0 : (src == 1 ? p.b_split0 : p.b_split1)) + row_in;
       }
@@ -110,10 +123,22 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
       lds_piece[j] = BM * PPR + blk * 64;
     }
   }
+  const int KT = p.K / BK;
+  const int kb = (int)(((int64_t)KT * blockIdx.y) / gridDim.y);       // this slice's K steps
+  const int ke = (int)(((int64_t)KT * (blockIdx.y + 1)) / gridDim.y);
+  const int k_off = STREAM ? n_tile % (ke - kb) : 0;  // where in the slice this tile starts
   auto issue = [&](int kt, int stg) __attribute__((always_inline)) {
+    if (STREAM) {
+      kt += k_off;
+      if (kt >= ke) kt -= ke - kb;
+    }
 #pragma unroll
-    for (int j = 0; j < IPW; ++j)
-      ld16_to_lds<false>(gbase[j] + kt * 2 * BK, lane_off[j], &lds[stg * STAGE + lds_piece[j]]);
+    for (int j = 0; j < IPW; ++j) {
+      const char* src = gbase[j] + kt * 2 * BK;
+      u32x4* dst = &lds[stg * STAGE + lds_piece[j]];
+      if (WNT && (j * NW + wave) % NI >= NIA) ld16_to_lds<true>(src, lane_off[j], dst);
+      else ld16_to_lds<false>(src, lane_off[j], dst);
+    }
   };
 
   f32x4 acc[MT][NT];
@@ -124,9 +149,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
 
   // Steps past the last re-load the last one (into a stage no later step
   // reads), so every step issues the same loads and one vmcnt value fits all.
-  const int KT = p.K / BK;
-  const int kb = (int)(((int64_t)KT * blockIdx.y) / gridDim.y);       // this slice's K steps
-  const int ke = (int)(((int64_t)KT * (blockIdx.y + 1)) / gridDim.y);
 #pragma unroll
   for (int st = 0; st < S - 1; ++st) issue(min(kb + st, ke - 1), st);
   int stg = 0;
@@ -174,6 +196,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
 
   // Lane holds C[16i + 4la + r][16j + li] of the wave tile.
   bool oor = false;  // an fp16 SwiGLU output out of fp16's range
+  const int cols = STREAM ? p.N - n0 - wn * WN : WN;  // columns from the wave's first to the last
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
 #pragma unroll
@@ -183,10 +206,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
       if (PART) {
         float* prow = p.part + ((int64_t)blockIdx.y * p.M + m) * p.N + n0 + wn * WN + li;
 #pragma unroll
-        for (int j = 0; j < NT; ++j) prow[16 * j] = acc[i][j][r];
+        for (int j = 0; j < NT; ++j)
+          if (16 * j < cols) prow[16 * j] = acc[i][j][r];
       } else if (EPI == kEpiSwiglu) {
 #pragma unroll
         for (int j = 0; j < NT; j += 2) {
+          if (16 * j >= cols) continue;
           const int pair = (wn * WN + 16 * j) >> 5;
           const int n = n_tile * (BN / 2) + 16 * pair + li;
           const float gt = acc[i][j][r], up = acc[i][j + 1][r];
@@ -197,6 +222,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
       } else {
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
+          if (16 * j >= cols) continue;
           const int n = n0 + wn * WN + 16 * j + li;
           float v = acc[i][j][r];
           if (EPI == kEpiResidRow)
@@ -670,36 +696,48 @@ hipError_t launch_reduce_norm(const GemmParams& p, int ksplit, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WGM, int WGN, int S, int BK, bool PART, bool WB>
+template <int BM, int BN, int WGM, int WGN, int S, int BK, bool ST, bool PART, bool WB>
 hipError_t launch_tile_k(Epilogue epi, const GemmParams& p, dim3 grid, hipStream_t s) {
   const dim3 block(64 * WGM * WGN);
+  if constexpr (PART) {  // the reduction applies the epilogue: only SwiGLU's order of the columns differs
+    if (epi == kEpiSwiglu) {
+      if constexpr ((BN / WGN) % 32 == 0)
+        hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiSwiglu, PART, WB>), grid, block, 0, s, p);
+      else
+        return hipErrorInvalidValue;
+    } else {
+      hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiStore, PART, WB>), grid, block, 0, s, p);
+    }
+    return hipGetLastError();
+  } else {
   switch (epi) {
-    case kEpiStore: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, kEpiStore, PART, WB>), grid, block, 0, s, p); break;
-    case kEpiResidRow: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, kEpiResidRow, PART, WB>), grid, block, 0, s, p); break;
-    case kEpiResidF32: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, kEpiResidF32, PART, WB>), grid, block, 0, s, p); break;
-    case kEpiRowScale: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, kEpiRowScale, PART, WB>), grid, block, 0, s, p); break;
+    case kEpiStore: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiStore, PART, WB>), grid, block, 0, s, p); break;
+    case kEpiResidRow: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiResidRow, PART, WB>), grid, block, 0, s, p); break;
+    case kEpiResidF32: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiResidF32, PART, WB>), grid, block, 0, s, p); break;
+    case kEpiRowScale: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiRowScale, PART, WB>), grid, block, 0, s, p); break;
     case kEpiSwiglu:
       if constexpr ((BN / WGN) % 32 == 0)
-        hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, kEpiSwiglu, PART, WB>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiSwiglu, PART, WB>), grid, block, 0, s, p);
       else
         return hipErrorInvalidValue;
       break;
   }
   return hipGetLastError();
+  }
 }
 
 // K split ksplit ways (ksplit > 1: fp32 partials in p.part, then gemm_reduce).
-template <int BM, int BN, int WGM, int WGN, int S, int BK>
+template <int BM, int BN, int WGM, int WGN, int S, int BK, bool ST = false>
 hipError_t launch_tile(Epilogue epi, const GemmParams& p, int ksplit, hipStream_t s) {
   if (p.K % BK || p.K / BK < ksplit) return hipErrorInvalidValue;  // slices of whole steps, maybe uneven
-  const dim3 grid(((p.M + BM - 1) / BM) * (p.N / BN), ksplit);
+  const dim3 grid(((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN), ksplit);
   hipError_t e;
   if (ksplit > 1)
-    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, true, false>(epi, p, grid, s)
-                : launch_tile_k<BM, BN, WGM, WGN, S, BK, true, true>(epi, p, grid, s);
+    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, true, false>(epi, p, grid, s)
+                : launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, true, true>(epi, p, grid, s);
   else
-    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, false, false>(epi, p, grid, s)
-                : launch_tile_k<BM, BN, WGM, WGN, S, BK, false, true>(epi, p, grid, s);
+    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, false, false>(epi, p, grid, s)
+                : launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, false, true>(epi, p, grid, s);
   if (e != hipSuccess || ksplit == 1) return e;
   return launch_gemm_reduce(epi, p, ksplit, BN, s);
 }
@@ -717,21 +755,29 @@ hipError_t launch_tile(Epilogue epi, const GemmParams& p, int ksplit, hipStream_
 // residual products whose 256 x 256 or 256 x 128 grids end in a partial round
 // (8192 x 5120: 1024 tiles, four whole rounds); index 12 is 256 x 192 with
 // 64-deep steps, double-buffered, for SwiGLU grids of one round (512 x 24576 x
-// 4096: 119 us against 124 us in 32-deep steps).
+// 4096: 119 us against 124 us in 32-deep steps).  Index 13 is 256 x 160 for SwiGLU
+// grids that it puts in fewer rounds (256 x 34816 x 5120: 113 us, one round of 218,
+// against 140; 512 x 19456 x 2560: 56 against 71).  From there (kStreamTiles) on the
+// tiles are STREAM ones; those after it serve products of at most 256 rows (see
+// stream_choice), with as many 64-deep stages as fit in LDS.
 struct TileShape { int bm, bn, wgm, wgn, bk; };
-constexpr int kNumTiles = 13;
+constexpr int kNumTiles = 28, kStreamTiles = 13;
 constexpr TileShape kTiles[kNumTiles] = {
     {256, 256, 2, 4, 32}, {256, 192, 4, 2, 32}, {256, 128, 4, 2, 64}, {128, 64, 4, 2, 64},
     {64, 64, 2, 2, 64},   {32, 64, 1, 2, 64},   {16, 32, 1, 1, 64},  {16, 16, 1, 1, 64},
     {16, 32, 1, 1, 32},   {32, 128, 1, 4, 64},  {256, 256, 4, 2, 64}, {256, 160, 4, 2, 64},
-    {256, 192, 4, 2, 64}};
+    {256, 192, 4, 2, 64}, {256, 160, 8, 1, 64},
+    {16, 64, 1, 4, 64},   {16, 96, 1, 3, 64},   {16, 160, 1, 5, 64},  {32, 96, 2, 1, 64},  {32, 160, 1, 5, 64},
+    {64, 64, 4, 1, 64},   {64, 96, 4, 1, 64},   {64, 128, 4, 1, 64},  {64, 160, 4, 1, 64}, {128, 96, 4, 1, 64},
+    {128, 128, 4, 2, 64}, {128, 160, 4, 1, 64}, {32, 128, 1, 4, 64},  {128, 64, 4, 2, 64}};
 constexpr int kOrderSwiglu[9] = {0, 1, 2, 3, 4, 5, 6, 7, 8};
 constexpr int kOrderResid[9] = {2, 1, 0, 3, 4, 5, 6, 7, 8};
 
 bool tile_ok(const GemmParams& p, Epilogue epi, const TileShape& t) {
-  if (p.N % t.bn || p.K % t.bk) return false;
+  const int unit = &t >= &kTiles[kStreamTiles] ? 32 : t.bn;  // ragged columns
+  if (p.N % unit || p.K % t.bk) return false;
   if (epi == kEpiSwiglu) return (t.bn / t.wgn) % 32 == 0;
-  return p.b_split0 % t.bn == 0 && p.b_split1 % t.bn == 0;
+  return p.b_split0 % unit == 0 && p.b_split1 % unit == 0;
 }
 
 hipError_t launch_tile_index(int c, Epilogue epi, const GemmParams& p, int ksplit, hipStream_t s) {
@@ -749,6 +795,21 @@ hipError_t launch_tile_index(int c, Epilogue epi, const GemmParams& p, int kspli
     case 10: return launch_tile<256, 256, 4, 2, 2, 64>(epi, p, ksplit, s);
     case 11: return launch_tile<256, 160, 4, 2, 3, 64>(epi, p, ksplit, s);
     case 12: return launch_tile<256, 192, 4, 2, 2, 64>(epi, p, ksplit, s);
+    case 13: return launch_tile<256, 160, 8, 1, 3, 64, true>(epi, p, ksplit, s);
+    case 14: return launch_tile<16, 64, 1, 4, 14, 64, true>(epi, p, ksplit, s);
+    case 15: return launch_tile<16, 96, 1, 3, 10, 64, true>(epi, p, ksplit, s);
+    case 16: return launch_tile<16, 160, 1, 5, 7, 64, true>(epi, p, ksplit, s);
+    case 17: return launch_tile<32, 96, 2, 1, 8, 64, true>(epi, p, ksplit, s);
+    case 18: return launch_tile<32, 160, 1, 5, 6, 64, true>(epi, p, ksplit, s);
+    case 19: return launch_tile<64, 64, 4, 1, 8, 64, true>(epi, p, ksplit, s);
+    case 20: return launch_tile<64, 96, 4, 1, 7, 64, true>(epi, p, ksplit, s);
+    case 21: return launch_tile<64, 128, 4, 1, 6, 64, true>(epi, p, ksplit, s);
+    case 22: return launch_tile<64, 160, 4, 1, 5, 64, true>(epi, p, ksplit, s);
+    case 23: return launch_tile<128, 96, 4, 1, 5, 64, true>(epi, p, ksplit, s);
+    case 24: return launch_tile<128, 128, 4, 2, 5, 64, true>(epi, p, ksplit, s);
+    case 25: return launch_tile<128, 160, 4, 1, 4, 64, true>(epi, p, ksplit, s);
+    case 26: return launch_tile<32, 128, 1, 4, 6, 64, true>(epi, p, ksplit, s);
+    case 27: return launch_tile<128, 64, 4, 2, 6, 64, true>(epi, p, ksplit, s);
   }
   return hipErrorInvalidValue;
 }
@@ -838,8 +899,54 @@ static int whole_round_columns(const GemmParams& p, int cus, double other, doubl
   if (p.N % 256 || t10 <= cus || whole == t10 || whole % mt) return 0;
   const int na = (int)(whole / mt);
   const long tail2 = (long)mt * (nt - na) * 2;
-  const double cost = (double)(whole / cus) * 65536.0 + (double)((tail2 + cus - 1) / cus) * 32768.0 / rate2;
+  // (and the second launch: about 4 us, in the unit of the others)
+  const double cost = (double)(whole / cus) * 65536.0 + (double)((tail2 + cus - 1) / cus) * 32768.0 / rate2 + 1e7 / p.K;
   return cost < other ? na : 0;
+}
+
+// Products of at most 256 rows stream the weights: one round of workgroups, each
+// with as many 64-deep stages in flight as its LDS holds, is the shape that
+// reads them fastest, and a second round or a half-empty one costs as much as a
+// whole one.  SwiGLU (up to 128 rows) takes the column width that covers
+// N in the fewest columns per compute unit; the other epilogues the width and
+// the number of K slices with the least
+//   width x steps + rows x steps / 2 + 0.16 x partial sums per compute unit
+// (+ 200, about 0.7 us, past four slices: the reduction's second round of loads),
+// steps being a slice's: weights, activations (from the L2) and the reduction, in
+// the proportions of the times measured at 64 and 128 rows.  Measured, fp16
+// weights, before -> now, 128 rows: SwiGLU 24576 x 4096 60.8 -> 41.8 us, 34816 x 5120
+// 127.9 -> 77.8, 19456 x 2560 39.3 -> 32.3, 5120 x 17408 73.6 -> 44.2 (eight slices),
+// 4096 x 12288 33.4 -> 30.8, 6144 x 4096 27.0 -> 20.2; 64 rows: 55.4 -> 34.5, 129.4 ->
+// 70.0, 37.1 -> 25.7, 58.3 -> 40.0, 27.3 -> 26.8, 23.1 -> 17.3; 16 rows: SwiGLU 42.6 ->
+// 33.6, 97.9 -> 65.1, 29.3 -> 21.5; 256 rows: 4096 x 4096 26.2 -> 22.4, 4096 x 12288
+// 52.4 -> 43.0, 2560 x 9728 42.1 -> 28.8.  Returns the tile, or -1 where no choice fills
+// half the compute units (narrow heads: the smaller tiles below).
+static int stream_choice(Epilogue epi, const GemmParams& p, int cus, int* ksplit) {
+  static constexpr int kBy16[] = {14}, kBy32[] = {26, 18}, kBy64[] = {19, 20, 21, 22}, kBy128[] = {27, 23, 24, 25};
+  static constexpr int kGate16[] = {15, 16}, kGate32[] = {17, 18}, kGate64[] = {20, 22}, kGate128[] = {23, 25};
+  const bool gate = epi == kEpiSwiglu;
+  const int* cand = p.M <= 16 ? (gate ? kGate16 : kBy16) : p.M <= 32 ? (gate ? kGate32 : kBy32)
+                    : p.M <= 64 ? (gate ? kGate64 : kBy64) : (gate ? kGate128 : kBy128);
+  const int n = gate ? 2 : p.M <= 16 ? 1 : p.M <= 32 ? 2 : 4;
+  int best = -1;
+  double best_cost = 0.0;
+  for (int i = 0; i < n; ++i) {
+    const TileShape& t = kTiles[cand[i]];
+    if (!tile_ok(p, epi, t)) continue;
+    const long tiles = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
+    const int KT = p.K / t.bk;
+    for (int ks = 1; ks <= (gate ? 1 : 8); ++ks) {
+      if (ks > 1 && (tiles * ks > cus || KT < 4 * ks || !p.part ||
+                     (size_t)ks * p.M * p.N * sizeof(float) > p.part_bytes))
+        break;
+      if (2 * tiles * ks < cus) continue;
+      const double rounds = (double)((tiles * ks + cus - 1) / cus);
+      const double steps = rounds * ((KT + ks - 1) / ks);
+      const double cost = steps * (t.bn + 0.5 * t.bm) + (ks > 1 ? 0.16 * ks * p.M * p.N / cus : 0.0) + (ks > 4 ? 200.0 : 0.0);
+      if (best < 0 || cost < best_cost) { best = cand[i]; best_cost = cost; *ksplit = ks; }
+    }
+  }
+  return best;
 }
 
 hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t s) {
@@ -862,12 +969,32 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // tiles (8 row tiles by 4 column tiles with 32 compute units per XCD)
   if (p.group_m < 1) p.group_m = 8;
   auto fits = [&](int ks) { return p.part && (size_t)ks * p.M * p.N * sizeof(float) <= p.part_bytes; };
+  // The streaming tiles.  SwiGLU: up to 128 rows.  Up to 16 rows, the other
+  // epilogues: long K of matrices wider than gemm_rows takes (5120 x 17408: 37 us
+  // against 44 for the one-wave tiles; 6144 x 4096 stays there, 12.9 us against 15.7),
+  // and from 13 rows and K = 9216 those it would take (16 rows: 2560 x 9728 21.7 -> 17.5
+  // us, 4096 x 12288 27.2 -> 24.8; at 9 rows 18.4 -> 17.2 and 23.7 -> 24.6; 13 rows of 4096 x
+  // 8192: 17.6 against 18.7).  17-128 rows, unless
+  // gemm_rows below covers them with a workgroup per compute unit.  129-256 rows: K
+  // of 4096 or more, not the QKV product (7168 x 5120: 37.7 us on the plan below, 39.0).
+  const int rows_cols = epi == kEpiSwiglu ? 32 : 16;
+  const bool rows_fit = (int64_t)(p.N / rows_cols) * ((p.M + 15) / 16) <= cus;
+  const bool stream = epi == kEpiSwiglu ? p.M <= 128 && !(p.M > 16 && rows_fit)
+                      : p.M <= 16       ? (rows_fit ? p.M > 12 && p.K >= 9216 : p.K >= 8192)
+                      : p.M <= 128      ? !rows_fit
+                                        : p.M <= 256 && p.K >= 4096 && epi != kEpiStore;
+  if (stream) {
+    int ks = 1;
+    const int t = stream_choice(epi, p, cus, &ks);
+    if (t >= 0) {
+      return launch_tile_index(t, epi, p, ks, s);
+    }
+  }
   // gemm_rows: at most one workgroup per compute unit (16 rows of matrices up to
   // 4096 wide, more rows of narrower ones), and SwiGLU on up to 16 rows.  Wider
   // products on few rows keep the one-wave tiles below: their tiles do not divide
   // evenly over the compute units either way, and one wave each balances better
-  // (5 rows: 6144 x 4096 12.5 us against 13.5, 5120 x 17408 42.0 us against 47.9).
-  const int rows_cols = epi == kEpiSwiglu ? 32 : 16;
+  // (5 rows: 6144 x 4096 12.5 us against 13.5).
   if (((epi == kEpiSwiglu && p.M <= 16) || (int64_t)(p.N / rows_cols) * ((p.M + 15) / 16) <= cus) && p.N % rows_cols == 0 &&
       (epi == kEpiSwiglu || (p.b_split0 % 16 == 0 && p.b_split1 % 16 == 0)))
     return launch_gemm_rows(epi, p, s);
@@ -883,15 +1010,17 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   }
   // K of 4096 or more with a few hundred rows (o and down on 129-1024 rows):
   // 256 x 128 tiles with K split re-read the activations and weights half as
-  // often as 128 x 64 tiles at the same workgroup count.  As many slices (2-4,
+  // often as 128 x 64 tiles at the same workgroup count.  As many slices (2-4, on more
+  // than 256 rows and K of 8192 up to 6,
   // of whole 64-deep steps, not necessarily equal) as keep the grid within one
   // round (1024 x 2560 x 9728, 80 tiles: 76 us in three slices against 94 us in
   // two; 1024 x 2560 x 4096: 41 us against 47; 512 x 4096 x 4096, 64 tiles: 38
   // us in four against 41 us for 256 tiles of 128 x 64; 512 x 4096 x 12288: 77
-  // us in four against 111 us in two).
+  // us in four against 111 us in two; 512 x 2560 x 9728, 40 tiles: 40.5 us in six
+  // against 46.4 in four).
   if (epi != kEpiSwiglu && p.M > 128 && p.M <= 1024 && p.K >= 4096 && tile_ok(p, epi, kTiles[2])) {
     const long tiles = (long)((p.M + 255) / 256) * (p.N / 128);
-    const int ks = (int)std::min<long>(4, std::max<long>(2, cus / tiles));
+    const int ks = (int)std::min<long>(p.M > 256 && p.K >= 8192 ? 6 : 4, std::max<long>(2, cus / tiles));
     if (p.K % 64 == 0 && p.K / 64 >= 8 * ks && fits(ks)) return launch_tile_index(2, epi, p, ks, s);
   }
   // 33..256 rows, epilogues other than SwiGLU (o, down, the fusion products):
@@ -914,7 +1043,7 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
     for (int i = 0; i < n; ++i) {
       const TileShape& t = kTiles[cand[i]];
       if (!tile_ok(p, epi, t)) continue;
-      const long tiles = (long)((p.M + t.bm - 1) / t.bm) * (p.N / t.bn);
+      const long tiles = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
       const double cost = (double)((tiles + cus - 1) / cus) * t.bm * t.bn / rate[i];
       if (best < 0 || cost < best_cost) { best = cand[i]; best_cost = cost; }
     }
@@ -930,15 +1059,15 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // 128 x 24576 x 4096, 256 x 128 (82 us) over 128 x 64 (87 us).
   const long tiles2 = (long)((p.M + 255) / 256) * (p.N / 128);
   if (epi == kEpiSwiglu && (p.M > 256 || (p.M >= 128 && 2 * tiles2 >= cus))) {
-    static const int cand[4] = {10, 0, 2, 12};
-    static const double rate[4] = {1.0, 0.91, 0.87, 0.855};
-    const int best = cheapest(cand, rate, 4);
+    static const int cand[5] = {10, 0, 2, 12, 13};
+    static const double rate[5] = {1.0, 0.91, 0.87, 0.855, 0.78};
+    const int best = cheapest(cand, rate, 5);
     // (1024 x 19456 x 2560: 124 us against 137 us for 608 tiles of 256 x 128
     // and 149 us for 304 of 256 x 256)
     if (best >= 0 && tile_ok(p, epi, kTiles[10])) {
       const TileShape& tb = kTiles[best];
-      const long tb_tiles = (long)((p.M + tb.bm - 1) / tb.bm) * (p.N / tb.bn);
-      const int bi = best == 10 ? 0 : best == 0 ? 1 : best == 2 ? 2 : 3;
+      const long tb_tiles = (long)((p.M + tb.bm - 1) / tb.bm) * ((p.N + tb.bn - 1) / tb.bn);
+      const int bi = best == 10 ? 0 : best == 0 ? 1 : best == 2 ? 2 : best == 12 ? 3 : 4;
       const int na = whole_round_columns(p, cus, (double)((tb_tiles + cus - 1) / cus) * tb.bm * tb.bn / rate[bi], 0.87);
       if (na > 0) {
         GemmParams qa = p;
@@ -970,7 +1099,7 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
     const int best = cheapest(cand, rate, 3);
     if (best >= 0 && tile_ok(p, epi, kTiles[10]) && p.b_split0 >= p.N) {
       const TileShape& tb = kTiles[best];
-      const long tb_tiles = (long)((p.M + tb.bm - 1) / tb.bm) * (p.N / tb.bn);
+      const long tb_tiles = (long)((p.M + tb.bm - 1) / tb.bm) * ((p.N + tb.bn - 1) / tb.bn);
       const int bi = best == 10 ? 0 : best == 11 ? 1 : 2;
       const int na = whole_round_columns(p, cus, (double)((tb_tiles + cus - 1) / cus) * tb.bm * tb.bn / rate[bi], 0.80);
       if (na > 0) {
