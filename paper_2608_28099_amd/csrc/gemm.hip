@@ -249,13 +249,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds(const GemmParams p) {
 // would only add a copy) U steps of 32 ahead, and the partial tiles are summed in
 // wave order through LDS.  Every output column then has NW waves of loads in
 // flight, without partial sums in memory or a second launch.
-// Measured, fp16 weights, against one wave per 16 columns through an LDS ring
-// (128 x 64 tiles for SwiGLU): 5 rows, 4096 x 4096 13.0 -> 10.2 us, 4096 x 12288
-// 30.6 -> 21.5 us (4.7 TB/s, launch included), 2560 x 9728 22.7 -> 16.6 us, SwiGLU
-// 24576 x 4096 53.5 -> 38.9 us (5.2 TB/s); 16 rows, SwiGLU 54.3 -> 45.2 us.  What
-// is left over the read is the A fragments, which every workgroup fetches from
-// its L2: 1 row takes 2-3 us less than 8.  Several row tiles: 20 rows of 512 x 768
-// 10.0 us as four 32 x 128 tiles, 5.6 us here.
+// Measured, fp16 weights, against one wave per 16 columns through an LDS ring: 5
+// rows, 4096 x 4096 13.0 -> 10.2 us, 4096 x 12288 30.6 -> 21.5 us (4.7 TB/s, launch
+// included), 2560 x 9728 22.7 -> 16.6 us.  What is left over the read is the A
+// fragments, which every workgroup fetches from its L2 (1 row takes 2-3 us less
+// than 8), so wide SwiGLU and more rows are faster on the streaming tiles (see
+// stream_choice).  Several row tiles: 20 rows of 512 x 768 10.0 us as four 32 x 128
+// tiles, 5.6 us here.
 // PK = 2 (at most 8 rows): a 16-row A fragment would be half repeats, so one load
 // brings two steps of the 8 rows (lanes li 0-7 the even step, 8-15 the odd one)
 // and the odd step's product takes the fragment rotated by 8 rows; rows 8-15 of
@@ -991,14 +991,15 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
     }
   }
   // gemm_rows: at most one workgroup per compute unit (16 rows of matrices up to
-  // 4096 wide, more rows of narrower ones), and SwiGLU on up to 16 rows.  Wider
+  // 4096 wide, more rows of narrower ones), and the SwiGLU of up to 16 rows that the
+  // streaming tiles leave.  Wider
   // products on few rows keep the one-wave tiles below: their tiles do not divide
   // evenly over the compute units either way, and one wave each balances better
   // (5 rows: 6144 x 4096 12.5 us against 13.5).
   if (((epi == kEpiSwiglu && p.M <= 16) || (int64_t)(p.N / rows_cols) * ((p.M + 15) / 16) <= cus) && p.N % rows_cols == 0 &&
       (epi == kEpiSwiglu || (p.b_split0 % 16 == 0 && p.b_split1 % 16 == 0)))
     return launch_gemm_rows(epi, p, s);
-  // 17..32 rows: the product streams the weights; a 32-row by 128-column tile
+  // 17..32 rows of what the streaming tiles leave: a 32-row by 128-column tile
   // with four waves, and K split so that the grid has enough workgroups in
   // flight (each slice at least 8 steps of 64).  (Up to 16 rows the one-wave
   // 16-row tiles below measured faster.)
@@ -1023,11 +1024,10 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
     const int ks = (int)std::min<long>(p.M > 256 && p.K >= 8192 ? 6 : 4, std::max<long>(2, cus / tiles));
     if (p.K % 64 == 0 && p.K / 64 >= 8 * ks && fits(ks)) return launch_tile_index(2, epi, p, ks, s);
   }
-  // 33..256 rows, epilogues other than SwiGLU (o, down, the fusion products):
-  // the weights stream with few tiles, so 128 x 64 tiles with K split until
-  // the grid has a workgroup per compute unit (9B-shaped down on 128 rows:
-  // 48 us against 70; o on 256 rows of the 27B shape: 58 us against 71).
-  // SwiGLU keeps its wide tiles, which measured faster there.
+  // 33..256 rows of the other epilogues that the streaming tiles leave (QKV on more
+  // than 128 rows, K under 4096 there, narrow matrices): 128 x 64 tiles with K split
+  // until the grid has a workgroup per compute unit (o on 256 rows of the 27B shape:
+  // 58 us against 71 for 256 x 128).
   if (epi != kEpiSwiglu && p.M > 32 && p.M <= 256 && tile_ok(p, epi, kTiles[3]) && p.part) {
     const long tiles = (long)((p.M + 127) / 128) * (p.N / 64);
     int ks = 2;
@@ -1054,9 +1054,8 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // leave most of them idle; the order below then takes smaller ones).  At
   // 1024 x 19456 x 2560 this takes 256 x 128 (608 tiles, 0.140 ms) over
   // 256 x 256 (304 tiles: two rounds, the second nearly empty, 0.154 ms); at
-  // 256 x 34816 x 5120 (last-row-only rows of the 27B shape) 256 x 256 in one
-  // round of 136 tiles (167 us) over 272 tiles of 256 x 128 (197 us); at
-  // 128 x 24576 x 4096, 256 x 128 (82 us) over 128 x 64 (87 us).
+  // 256 x 34816 x 5120 (last-row-only rows of the 27B shape) 256 x 160 in one round
+  // of 218 tiles (112 us) over 136 of 256 x 256 (140 us).
   const long tiles2 = (long)((p.M + 255) / 256) * (p.N / 128);
   if (epi == kEpiSwiglu && (p.M > 256 || (p.M >= 128 && 2 * tiles2 >= cus))) {
     static const int cand[5] = {10, 0, 2, 12, 13};
