@@ -99,10 +99,16 @@ __device__ __forceinline__ void softmax_pv_unit(RowState<HD, F16>& st, f32x4 s0,
   constexpr int NT = HD / 16;
   // sc = s - m, or s in the first unit
   float sc[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
+  // The mask of a tail unit.  The asm keeps it a branch that whole units skip: left to
+  // itself the compiler computed the mask and selected by it in every unit (24 of
+  // ~95 vector instructions of the one-tile loop; forward of the 131072-token batch
+  // 2936 -> 2905 us, 27B shape 6922 -> 6893).
   if (limit < 32) {
+    int lim = limit;
+    asm volatile("" : "+s"(lim));
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      if (8 * la + i >= limit) sc[i] = -INFINITY;
+      if (8 * la + i >= lim) sc[i] = -INFINITY;
   }
   float lmax = fmaxf(fmaxf(sc[0], sc[1]), sc[2]);
   lmax = fmaxf(fmaxf(lmax, sc[3]), sc[4]);
