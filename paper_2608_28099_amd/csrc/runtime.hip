@@ -527,12 +527,11 @@ int check_forward(const sp_probe_config& c, const Plan& pl, const sp_kv_cache* k
 // once: an order would only cost each workgroup a dependent load.  A ragged batch
 // of one round needs it as much as a longer grid: without it the slots past its
 // short sequences' ends fall on some compute units and spare others (8 sequences
-// of 7451-59610 tokens: 353 us per forward with the list, 408 without).  Nor are
-// more than 16384 sequences ordered: the ranking is quadratic in them (one
-// workgroup beside the rotations), and a grid of that many rounds has no tail to
-// fill.
+// of 7451-59610 tokens, 9B-shaped head, five soft rows: 270 us per forward with the
+// list, 298 without; 20000 of 64-2048 tokens on a small head: 781 against 909).
+// Batches of many alike sequences pay up to 2% for it.
 bool needs_work_list(const Ctx& x, const AttnPlan& a, int batch) {
-  if (x.cfg->dtype != SP_BF16 || batch == 1 || batch > 16384) return false;
+  if (x.cfg->dtype != SP_BF16 || batch == 1) return false;
   return a.max_splits > 1 || (int64_t)x.cfg->n_kv_heads * a.n_qgroups * batch > attn_slots(*x.cfg, a, x.n_cus);
 }
 

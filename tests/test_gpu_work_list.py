@@ -1,0 +1,72 @@
+"""The order in which the split attention takes its items, over batch sizes at the
+edges of the list writer's passes (256 and 1024 sequences) and far past them:
+every (sequence, split) is in the list once, and writing it costs time in
+proportion to the sequences."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_28099_amd import binding, configs, inputs
+
+pytestmark = pytest.mark.gpu
+
+# split_len 256: none to six splits, full last ones, ties and an empty sequence
+LENS = (700, 0, 256, 1, 1536, 257, 255, 1025, 256, 1300, 37)
+
+
+def _probe(batch):
+    """A head over eleven stored sequences and a handle for `batch` that repeat them."""
+    dev = torch.device("cuda:0")
+    w = configs.Workload(name="list", dtype="bf16", batch=len(LENS), k=1, hidden=64, n_q_heads=2, n_kv_heads=1,
+                         head_dim=64, intermediate=64, n_classes=2, seq_len=("list", LENS), kv_std=1.5,
+                         weight_std=0.1, seed=17)
+    return (w, inputs.kv_cache(w, inputs.seq_lens(w), dev), inputs.params(w, dev),
+            binding.Probe(w, max_batch=batch, max_seq_len=max(LENS), split_len=256))
+
+
+def _pick(kv, order):
+    idx = torch.as_tensor(order, device=kv.pool.device)
+    return inputs.KVCache(kv.pool, kv.block_table[idx].contiguous(), kv.seq_lens[idx].contiguous(), kv.block_size,
+                          kv.max_blocks_per_seq, kv.n_kv, kv.head_dim)
+
+
+@pytest.mark.parametrize("batch", [2, 255, 257, 1023, 1025, 4099, 20000])
+def test_every_split_is_taken_once(batch):
+    """A row's attention output does not depend on the batch it comes in, so each
+    equals the one of its sequence alone, bit for bit.  A missing item would leave
+    the partial that the call before wrote for another sequence."""
+    w, kv, params, probe = _probe(batch)
+    row = w.n_q_heads * w.head_dim
+
+    def attn(order):
+        probe.forward(_pick(kv, order), params)
+        tap = probe.tap(binding.SP_TAP_ATTN, len(order), kv.pool.device).view(torch.float16)
+        return tap[:len(order) * row].reshape(-1, row)
+
+    alone = torch.cat([attn([i]).clone() for i in range(len(LENS))])
+    for order in ([i % len(LENS) for i in range(batch)], [(3 * i + 5) % len(LENS) for i in reversed(range(batch))]):
+        assert torch.equal(attn(order), alone[torch.as_tensor(order, device=kv.pool.device)])
+    assert probe.check_device_error() == binding.SP_OK
+    probe.close()
+
+
+def test_time_grows_with_the_sequences():
+    """Four times the sequences take about four times as long; ranking every pair of
+    them took fifteen times as long.  Eight lies between, twofold from either."""
+    best = {}
+    for batch in (4096, 16384):
+        w, kv, params, probe = _probe(batch)
+        sub = _pick(kv, np.random.Generator(np.random.PCG64(3)).integers(0, len(LENS), size=batch))
+        logits = torch.empty((batch, w.n_classes), dtype=torch.float32, device=kv.pool.device)
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                probe.forward(sub, params, logits=logits)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) / 4)
+        best[batch] = min(times)
+        probe.close()
+    assert best[16384] <= 8 * best[4096], best
