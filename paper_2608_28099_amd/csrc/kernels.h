@@ -53,7 +53,7 @@ struct RopeParams {
   // dispatch order (longest first) for splits of split_len tokens: every split
   // that is not its sequence's last (split_len tokens each), by sequence and
   // split; then each sequence's last split (split 0 of an empty sequence), by
-  // token count descending, ties by sequence.  items holds batch * (splits of
+  // token count descending (to a 1024th of a split).  items holds batch * (splits of
   // max_seq_len) pairs (sequence, split); *n_items receives the number written.
   int2* items;
   int* n_items;
