@@ -995,8 +995,13 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // streaming tiles leave.  Wider
   // products on few rows keep the one-wave tiles below: their tiles do not divide
   // evenly over the compute units either way, and one wave each balances better
-  // (5 rows: 6144 x 4096 12.5 us against 13.5).
-  if (((epi == kEpiSwiglu && p.M <= 16) || (int64_t)(p.N / rows_cols) * ((p.M + 15) / 16) <= cus) && p.N % rows_cols == 0 &&
+  // (5 rows: 6144 x 4096 12.5 us against 13.5).  More rows of narrow matrices leave
+  // most compute units idle, so past K = 4096 the plans below split K over
+  // workgroups too (32 rows of 1024 x 4096: 9.9 us here, 10.3 in eight slices; 512 x 8192
+  // 16.7 and 10.8; 1024 x 28672 52.2 and 24.5; 64 rows of it 52.2 and 28.2).
+  const bool split_narrow = epi != kEpiSwiglu && p.M > 16 && p.M <= 128 && p.K > 4096 &&
+                            tile_ok(p, epi, kTiles[p.M <= 32 ? 9 : 3]) && fits(8);
+  if (((epi == kEpiSwiglu && p.M <= 16) || (rows_fit && !split_narrow)) && p.N % rows_cols == 0 &&
       (epi == kEpiSwiglu || (p.b_split0 % 16 == 0 && p.b_split1 % 16 == 0)))
     return launch_gemm_rows(epi, p, s);
   // 17..32 rows of what the streaming tiles leave: a 32-row by 128-column tile
