@@ -529,9 +529,10 @@ int check_forward(const sp_probe_config& c, const Plan& pl, const sp_kv_cache* k
 // short sequences' ends fall on some compute units and spare others (8 sequences
 // of 7451-59610 tokens, 9B-shaped head, five soft rows: 270 us per forward with the
 // list, 298 without; 20000 of 64-2048 tokens on a small head: 781 against 909).
-// Batches of many alike sequences pay up to 2% for it.
+// Batches of many alike sequences pay up to 2% for it.  The list's writer is one
+// more row of the RoPE launch's grid, which has at most 65535.
 bool needs_work_list(const Ctx& x, const AttnPlan& a, int batch) {
-  if (x.cfg->dtype != SP_BF16 || batch == 1) return false;
+  if (x.cfg->dtype != SP_BF16 || batch == 1 || batch >= 65535) return false;
   return a.max_splits > 1 || (int64_t)x.cfg->n_kv_heads * a.n_qgroups * batch > attn_slots(*x.cfg, a, x.n_cus);
 }
 
