@@ -410,7 +410,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32(const GemmParams p) {
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, la = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_out = EPI == kEpiSwiglu ? p.N / 2 : p.N;
-  const int n0 = 16 * blockIdx.x, m0 = 16 * MT * blockIdx.y;
+  const int n0 = 16 * blockIdx.x;
+  const int64_t m_first = (int64_t)16 * MT * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z);
+  if (m_first >= p.M) return;  // the grid's last layer may be partial
+  const int m0 = (int)m_first;
   const int KT = (p.K + 15) / 16, kb = KT * wave / NW, ke = KT * (wave + 1) / NW;
 
   const float* ap[MT];
@@ -491,16 +494,18 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32(const GemmParams p) {
 }
 
 // Four row tiles per workgroup (each weight fragment then serves 64 rows) where
-// that still leaves a workgroup per compute unit, else one.
+// that still leaves a workgroup per compute unit, else one.  Row tiles past the
+// 65535 of the grid's y go to further layers in z.
 template <int EPI>
 hipError_t launch_f32(const GemmParams& p, hipStream_t s) {
-  if (p.K % 4 || p.lda % 4 || p.ldb % 4 || p.M > 16 * 65535) return hipErrorInvalidValue;
+  if (p.K % 4 || p.lda % 4 || p.ldb % 4) return hipErrorInvalidValue;
   const int n_out = EPI == kEpiSwiglu ? p.N / 2 : p.N, cols = (n_out + 15) / 16;
   const int cus = p.n_cus > 0 ? p.n_cus : 256;
-  if (p.M > 16 && (int64_t)cols * ((p.M + 63) / 64) >= cus)
-    hipLaunchKernelGGL((gemm_f32<4, 8, EPI>), dim3(cols, (p.M + 63) / 64), dim3(512), 0, s, p);
-  else
-    hipLaunchKernelGGL((gemm_f32<1, 8, EPI>), dim3(cols, (p.M + 15) / 16), dim3(512), 0, s, p);
+  const bool four = p.M > 16 && (int64_t)cols * (((int64_t)p.M + 63) / 64) >= cus;
+  const int64_t tiles = ((int64_t)p.M + (four ? 63 : 15)) / (four ? 64 : 16);
+  const dim3 grid(cols, (unsigned)std::min<int64_t>(tiles, 65535), (unsigned)((tiles + 65534) / 65535)), block(512);
+  if (four) hipLaunchKernelGGL((gemm_f32<4, 8, EPI>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32<1, 8, EPI>), grid, block, 0, s, p);
   return hipGetLastError();
 }
 
