@@ -18,7 +18,7 @@
 // matching up rows, so every lane holds gate and up of the same outputs.
 // Split-K (PART, small M: the product then streams the weights with too few
 // workgroups to keep enough loads in flight): blockIdx.y takes a slice of the
-// K steps and writes its fp32 partial tile; gemm_reduce sums the slices in a
+// K steps and writes its fp32 partial tile; gemm_reduce4 sums the slices in a
 // fixed order and applies the epilogue.
 // Weights come either as the caller's bf16 matrices (WBF16, converted per
 // fragment) or as an fp16 image of them made once for the frozen head (no
@@ -509,41 +509,10 @@ hipError_t launch_f32(const GemmParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Sum of the split-K slices and the epilogue, one thread per output.  SwiGLU:
-// output o of tile o / (bn/2) has its gate column 32 ((o % (bn/2)) / 16) +
-// o % 16 in the tile's interleaved columns and its up column 16 later.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_reduce(const GemmParams p, int ksplit, int bn) {
-  const int n_out = EPI == kEpiSwiglu ? p.N / 2 : p.N;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)p.M * n_out) return;
-  const int m = (int)(idx / n_out), o = (int)(idx % n_out);
-  const int64_t slice = (int64_t)p.M * p.N;
-  const float* src = p.part + (int64_t)m * p.N;
-  if (EPI == kEpiSwiglu) {
-    const int w = o % (bn / 2);
-    const int g = (o / (bn / 2)) * bn + 32 * (w / 16) + w % 16;
-    float gt = 0.f, up = 0.f;
-    for (int k = 0; k < ksplit; ++k) {
-      gt += src[k * slice + g];
-      up += src[k * slice + g + 16];
-    }
-    const float v = silu(gt) * up;
-    ((f16*)p.c)[(int64_t)m * p.ldc + o] = (f16)v;
-    if (!(fabsf(v) <= 65504.0f) && p.status) atomicOr(p.status, kStatusRange);
-    return;
-  }
-  float v = 0.f;
-  for (int k = 0; k < ksplit; ++k) v += src[k * slice + o];
-  if (EPI == kEpiResidRow) v += (float)((const bf16*)p.r)[(int64_t)(m % p.r_mod) * p.r_ld + o];
-  if (EPI == kEpiResidF32) v += ((const float*)p.r)[(int64_t)m * p.r_ld + o];
-  if (EPI == kEpiRowScale) v *= ((const float*)p.r)[m];
-  ((float*)p.c)[(int64_t)m * p.ldc + o] = v;
-}
-
-// The same, four consecutive outputs per thread (16-byte partial loads) and
-// one output row per blockIdx.y; the launcher takes it when every row stride
-// and base keeps those accesses aligned.  Same sums in the same order.
+// Sum of the split-K slices and the epilogue, four consecutive outputs per thread
+// (16-byte partial loads) and one output row per blockIdx.y.  SwiGLU: output o of
+// tile o / (bn/2) has its gate column 32 ((o % (bn/2)) / 16) + o % 16 in the tile's
+// interleaved columns and its up column 16 later.
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_reduce4(const GemmParams p, int ksplit, int bn) {
   const int n_out = EPI == kEpiSwiglu ? p.N / 2 : p.N;
@@ -701,48 +670,49 @@ hipError_t launch_reduce_norm(const GemmParams& p, int ksplit, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WGM, int WGN, int S, int BK, bool ST, bool PART, bool WB>
+// What launch_gemm asks of a tile; the kernels of the rest are not built.
+enum : int { kGate = 1, kGateSplit = 2, kPlain = 4, kPlainSplit = 8 };  // SwiGLU, the other epilogues; with K split
+
+template <int BM, int BN, int WGM, int WGN, int S, int BK, int USE, bool ST, bool PART, bool WB>
 hipError_t launch_tile_k(Epilogue epi, const GemmParams& p, dim3 grid, hipStream_t s) {
   const dim3 block(64 * WGM * WGN);
-  if constexpr (PART) {  // the reduction applies the epilogue: only SwiGLU's order of the columns differs
-    if (epi == kEpiSwiglu) {
-      if constexpr ((BN / WGN) % 32 == 0)
-        hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiSwiglu, PART, WB>), grid, block, 0, s, p);
-      else
-        return hipErrorInvalidValue;
-    } else {
+  if (epi == kEpiSwiglu) {
+    if constexpr ((USE & (PART ? kGateSplit : kGate)) != 0) {
+      static_assert((BN / WGN) % 32 == 0, "a wave holds whole pairs of gate and up columns");
+      hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiSwiglu, PART, WB>), grid, block, 0, s, p);
+      return hipGetLastError();
+    }
+  } else if constexpr ((USE & (PART ? kPlainSplit : kPlain)) != 0) {
+    if constexpr (PART) {  // the reduction applies the epilogue
       hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiStore, PART, WB>), grid, block, 0, s, p);
+    } else {
+      switch (epi) {
+        case kEpiStore: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiStore, PART, WB>), grid, block, 0, s, p); break;
+        case kEpiResidRow: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiResidRow, PART, WB>), grid, block, 0, s, p); break;
+        case kEpiResidF32: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiResidF32, PART, WB>), grid, block, 0, s, p); break;
+        case kEpiRowScale: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiRowScale, PART, WB>), grid, block, 0, s, p); break;
+        case kEpiSwiglu: break;
+      }
     }
     return hipGetLastError();
-  } else {
-  switch (epi) {
-    case kEpiStore: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiStore, PART, WB>), grid, block, 0, s, p); break;
-    case kEpiResidRow: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiResidRow, PART, WB>), grid, block, 0, s, p); break;
-    case kEpiResidF32: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiResidF32, PART, WB>), grid, block, 0, s, p); break;
-    case kEpiRowScale: hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiRowScale, PART, WB>), grid, block, 0, s, p); break;
-    case kEpiSwiglu:
-      if constexpr ((BN / WGN) % 32 == 0)
-        hipLaunchKernelGGL((gemm_lds<BM, BN, WGM, WGN, S, BK, ST, kEpiSwiglu, PART, WB>), grid, block, 0, s, p);
-      else
-        return hipErrorInvalidValue;
-      break;
   }
-  return hipGetLastError();
-  }
+  return hipErrorInvalidValue;
 }
 
-// K split ksplit ways (ksplit > 1: fp32 partials in p.part, then gemm_reduce).
-template <int BM, int BN, int WGM, int WGN, int S, int BK, bool ST = false>
+hipError_t launch_gemm_reduce(Epilogue epi, const GemmParams& p, int ksplit, int bn, hipStream_t s);
+
+// K split ksplit ways (ksplit > 1: fp32 partials in p.part, then the reduction).
+template <int BM, int BN, int WGM, int WGN, int S, int BK, int USE, bool ST = false>
 hipError_t launch_tile(Epilogue epi, const GemmParams& p, int ksplit, hipStream_t s) {
   if (p.K % BK || p.K / BK < ksplit) return hipErrorInvalidValue;  // slices of whole steps, maybe uneven
   const dim3 grid(((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN), ksplit);
   hipError_t e;
   if (ksplit > 1)
-    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, true, false>(epi, p, grid, s)
-                : launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, true, true>(epi, p, grid, s);
+    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, USE, ST, true, false>(epi, p, grid, s)
+                : launch_tile_k<BM, BN, WGM, WGN, S, BK, USE, ST, true, true>(epi, p, grid, s);
   else
-    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, false, false>(epi, p, grid, s)
-                : launch_tile_k<BM, BN, WGM, WGN, S, BK, ST, false, true>(epi, p, grid, s);
+    e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, USE, ST, false, false>(epi, p, grid, s)
+                : launch_tile_k<BM, BN, WGM, WGN, S, BK, USE, ST, false, true>(epi, p, grid, s);
   if (e != hipSuccess || ksplit == 1) return e;
   return launch_gemm_reduce(epi, p, ksplit, BN, s);
 }
@@ -787,87 +757,64 @@ bool tile_ok(const GemmParams& p, Epilogue epi, const TileShape& t) {
 
 hipError_t launch_tile_index(int c, Epilogue epi, const GemmParams& p, int ksplit, hipStream_t s) {
   switch (c) {
-    case 0: return launch_tile<256, 256, 2, 4, 3, 32>(epi, p, ksplit, s);
-    case 1: return launch_tile<256, 192, 4, 2, 3, 32>(epi, p, ksplit, s);
-    case 2: return launch_tile<256, 128, 4, 2, 3, 64>(epi, p, ksplit, s);
-    case 3: return launch_tile<128, 64, 4, 2, 6, 64>(epi, p, ksplit, s);
-    case 4: return launch_tile<64, 64, 2, 2, 8, 64>(epi, p, ksplit, s);
-    case 5: return launch_tile<32, 64, 1, 2, 8, 64>(epi, p, ksplit, s);
-    case 6: return launch_tile<16, 32, 1, 1, 8, 64>(epi, p, ksplit, s);
-    case 7: return launch_tile<16, 16, 1, 1, 8, 64>(epi, p, ksplit, s);
-    case 8: return launch_tile<16, 32, 1, 1, 8, 32>(epi, p, ksplit, s);
-    case 9: return launch_tile<32, 128, 1, 4, 6, 64>(epi, p, ksplit, s);
-    case 10: return launch_tile<256, 256, 4, 2, 2, 64>(epi, p, ksplit, s);
-    case 11: return launch_tile<256, 160, 4, 2, 3, 64>(epi, p, ksplit, s);
-    case 12: return launch_tile<256, 192, 4, 2, 2, 64>(epi, p, ksplit, s);
-    case 13: return launch_tile<256, 160, 8, 1, 3, 64, true>(epi, p, ksplit, s);
-    case 14: return launch_tile<16, 64, 1, 4, 14, 64, true>(epi, p, ksplit, s);
-    case 15: return launch_tile<16, 96, 1, 3, 10, 64, true>(epi, p, ksplit, s);
-    case 16: return launch_tile<16, 160, 1, 5, 7, 64, true>(epi, p, ksplit, s);
-    case 17: return launch_tile<32, 96, 2, 1, 8, 64, true>(epi, p, ksplit, s);
-    case 18: return launch_tile<32, 160, 1, 5, 6, 64, true>(epi, p, ksplit, s);
-    case 19: return launch_tile<64, 64, 4, 1, 8, 64, true>(epi, p, ksplit, s);
-    case 20: return launch_tile<64, 96, 4, 1, 7, 64, true>(epi, p, ksplit, s);
-    case 21: return launch_tile<64, 128, 4, 1, 6, 64, true>(epi, p, ksplit, s);
-    case 22: return launch_tile<64, 160, 4, 1, 5, 64, true>(epi, p, ksplit, s);
-    case 23: return launch_tile<128, 96, 4, 1, 5, 64, true>(epi, p, ksplit, s);
-    case 24: return launch_tile<128, 128, 4, 2, 5, 64, true>(epi, p, ksplit, s);
-    case 25: return launch_tile<128, 160, 4, 1, 4, 64, true>(epi, p, ksplit, s);
-    case 26: return launch_tile<32, 128, 1, 4, 6, 64, true>(epi, p, ksplit, s);
-    case 27: return launch_tile<128, 64, 4, 2, 6, 64, true>(epi, p, ksplit, s);
+    case 0: return launch_tile<256, 256, 2, 4, 3, 32, kPlain | kGate>(epi, p, ksplit, s);
+    case 1: return launch_tile<256, 192, 4, 2, 3, 32, kPlain | kGate>(epi, p, ksplit, s);
+    case 2: return launch_tile<256, 128, 4, 2, 3, 64, kPlain | kPlainSplit | kGate>(epi, p, ksplit, s);
+    case 3: return launch_tile<128, 64, 4, 2, 6, 64, kPlain | kPlainSplit | kGate>(epi, p, ksplit, s);
+    case 4: return launch_tile<64, 64, 2, 2, 8, 64, kPlain | kGate>(epi, p, ksplit, s);
+    case 5: return launch_tile<32, 64, 1, 2, 8, 64, kPlain | kGate>(epi, p, ksplit, s);
+    case 6: return launch_tile<16, 32, 1, 1, 8, 64, kPlain | kGate>(epi, p, ksplit, s);
+    case 7: return launch_tile<16, 16, 1, 1, 8, 64, kPlain>(epi, p, ksplit, s);
+    case 8: return launch_tile<16, 32, 1, 1, 8, 32, kPlain | kGate>(epi, p, ksplit, s);
+    case 9: return launch_tile<32, 128, 1, 4, 6, 64, kPlain | kPlainSplit | kGate | kGateSplit>(epi, p, ksplit, s);
+    case 10: return launch_tile<256, 256, 4, 2, 2, 64, kPlain | kPlainSplit | kGate>(epi, p, ksplit, s);
+    case 11: return launch_tile<256, 160, 4, 2, 3, 64, kPlain>(epi, p, ksplit, s);
+    case 12: return launch_tile<256, 192, 4, 2, 2, 64, kGate>(epi, p, ksplit, s);
+    case 13: return launch_tile<256, 160, 8, 1, 3, 64, kGate, true>(epi, p, ksplit, s);
+    case 14: return launch_tile<16, 64, 1, 4, 14, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 15: return launch_tile<16, 96, 1, 3, 10, 64, kGate, true>(epi, p, ksplit, s);
+    case 16: return launch_tile<16, 160, 1, 5, 7, 64, kGate, true>(epi, p, ksplit, s);
+    case 17: return launch_tile<32, 96, 2, 1, 8, 64, kGate, true>(epi, p, ksplit, s);
+    case 18: return launch_tile<32, 160, 1, 5, 6, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
+    case 19: return launch_tile<64, 64, 4, 1, 8, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 20: return launch_tile<64, 96, 4, 1, 7, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
+    case 21: return launch_tile<64, 128, 4, 1, 6, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 22: return launch_tile<64, 160, 4, 1, 5, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
+    case 23: return launch_tile<128, 96, 4, 1, 5, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
+    case 24: return launch_tile<128, 128, 4, 2, 5, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 25: return launch_tile<128, 160, 4, 1, 4, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
+    case 26: return launch_tile<32, 128, 1, 4, 6, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 27: return launch_tile<128, 64, 4, 2, 6, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
   }
   return hipErrorInvalidValue;
 }
 
-}  // namespace
-
 hipError_t launch_gemm_reduce(Epilogue epi, const GemmParams& p, int ksplit, int bn, hipStream_t s) {
   const int n_out = epi == kEpiSwiglu ? p.N / 2 : p.N;
-  auto al16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
-  const bool vec = n_out % 4 == 0 && p.N % 4 == 0 && p.ldc % 4 == 0 && al16(p.part) &&
-                   (epi == kEpiSwiglu ? ((uintptr_t)p.c & 7) == 0 && bn % 32 == 0 : al16(p.c)) &&
-                   (epi == kEpiResidRow ? p.r_ld % 4 == 0 && ((uintptr_t)p.r & 7) == 0 : true) &&
-                   (epi == kEpiResidF32 ? p.r_ld % 4 == 0 && al16(p.r) : true) && p.M <= 65535;
+  auto aligned = [](const void* q, uintptr_t to) { return ((uintptr_t)q & (to - 1)) == 0; };
+  // every row of a split product is 4 or more values wide and aligned to them
+  if (n_out % 4 || p.N % 4 || p.ldc % 4 || !aligned(p.part, 16) || p.M > 65535 ||
+      (epi == kEpiSwiglu ? !aligned(p.c, 8) || bn % 32 : !aligned(p.c, 16)) ||
+      (epi == kEpiResidRow && (p.r_ld % 4 || !aligned(p.r, 8))) || (epi == kEpiResidF32 && (p.r_ld % 4 || !aligned(p.r, 16))))
+    return hipErrorInvalidValue;
   // the norm that follows, where one is asked for (rows of up to 8192 values)
-  if (vec && p.norm_gain && p.norm_done && p.N <= 8192 && p.norm_ld % 4 == 0 && ((uintptr_t)p.norm_out & 7) == 0 &&
-      ((uintptr_t)p.norm_gain & 7) == 0 && ((uintptr_t)p.norm_gain2 & 7) == 0) {
-    if (epi == kEpiResidRow || epi == kEpiResidF32) {
-      *p.norm_done = true;
-      return epi == kEpiResidRow ? launch_reduce_norm<kEpiResidRow>(p, ksplit, s) : launch_reduce_norm<kEpiResidF32>(p, ksplit, s);
-    }
+  if ((epi == kEpiResidRow || epi == kEpiResidF32) && p.norm_gain && p.norm_done && p.N <= 8192 && p.norm_ld % 4 == 0 &&
+      aligned(p.norm_out, 8) && aligned(p.norm_gain, 8) && aligned(p.norm_gain2, 8)) {
+    *p.norm_done = true;
+    return epi == kEpiResidRow ? launch_reduce_norm<kEpiResidRow>(p, ksplit, s) : launch_reduce_norm<kEpiResidF32>(p, ksplit, s);
   }
-  if (vec) {
-    const dim3 g4((unsigned)((n_out / 4 + 255) / 256), (unsigned)p.M);
-    switch (epi) {
-      case kEpiStore: hipLaunchKernelGGL(gemm_reduce4<kEpiStore>, g4, dim3(256), 0, s, p, ksplit, bn); break;
-      case kEpiResidRow: hipLaunchKernelGGL(gemm_reduce4<kEpiResidRow>, g4, dim3(256), 0, s, p, ksplit, bn); break;
-      case kEpiResidF32: hipLaunchKernelGGL(gemm_reduce4<kEpiResidF32>, g4, dim3(256), 0, s, p, ksplit, bn); break;
-      case kEpiRowScale: hipLaunchKernelGGL(gemm_reduce4<kEpiRowScale>, g4, dim3(256), 0, s, p, ksplit, bn); break;
-      case kEpiSwiglu: hipLaunchKernelGGL(gemm_reduce4<kEpiSwiglu>, g4, dim3(256), 0, s, p, ksplit, bn); break;
-    }
-    return hipGetLastError();
-  }
-  const dim3 rgrid((unsigned)(((int64_t)p.M * n_out + 255) / 256));
+  const dim3 g4((unsigned)((n_out / 4 + 255) / 256), (unsigned)p.M);
   switch (epi) {
-    case kEpiStore: hipLaunchKernelGGL(gemm_reduce<kEpiStore>, rgrid, dim3(256), 0, s, p, ksplit, bn); break;
-    case kEpiResidRow: hipLaunchKernelGGL(gemm_reduce<kEpiResidRow>, rgrid, dim3(256), 0, s, p, ksplit, bn); break;
-    case kEpiResidF32: hipLaunchKernelGGL(gemm_reduce<kEpiResidF32>, rgrid, dim3(256), 0, s, p, ksplit, bn); break;
-    case kEpiRowScale: hipLaunchKernelGGL(gemm_reduce<kEpiRowScale>, rgrid, dim3(256), 0, s, p, ksplit, bn); break;
-    case kEpiSwiglu: hipLaunchKernelGGL(gemm_reduce<kEpiSwiglu>, rgrid, dim3(256), 0, s, p, ksplit, bn); break;
+    case kEpiStore: hipLaunchKernelGGL(gemm_reduce4<kEpiStore>, g4, dim3(256), 0, s, p, ksplit, bn); break;
+    case kEpiResidRow: hipLaunchKernelGGL(gemm_reduce4<kEpiResidRow>, g4, dim3(256), 0, s, p, ksplit, bn); break;
+    case kEpiResidF32: hipLaunchKernelGGL(gemm_reduce4<kEpiResidF32>, g4, dim3(256), 0, s, p, ksplit, bn); break;
+    case kEpiRowScale: hipLaunchKernelGGL(gemm_reduce4<kEpiRowScale>, g4, dim3(256), 0, s, p, ksplit, bn); break;
+    case kEpiSwiglu: hipLaunchKernelGGL(gemm_reduce4<kEpiSwiglu>, g4, dim3(256), 0, s, p, ksplit, bn); break;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_tile(Epilogue epi, const GemmParams& p, int tile, int ksplit, hipStream_t s) {
-  if (tile < 0 || tile >= kNumTiles || !tile_ok(p, epi, kTiles[tile]) || ksplit < 1) return hipErrorInvalidValue;
-  if (p.lda % 8 || p.ldb % 8) return hipErrorInvalidValue;
-  if (ksplit > 1 && (!p.part || (size_t)ksplit * p.M * p.N * sizeof(float) > p.part_bytes))
-    return hipErrorInvalidValue;
-  GemmParams q = p;
-  if (q.n_xcd < 1) q.n_xcd = 1;
-  if (q.group_m < 1) q.group_m = 1 << 30;
-  return launch_tile_index(tile, epi, q, ksplit, s);
-}
+}  // namespace
 
 // The columns [n1, N) of a product as a product of their own (same rows and
 // K): weights, output and residual offset by n1 columns.  SwiGLU counts n1 in

@@ -179,12 +179,6 @@ struct GemmParams {
 };
 // dt: storage dtype of the weights (kF32: fp32 matrix-core path; kBF16: fp16 MFMA path)
 hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p, hipStream_t s);
-// One tile shape of the fp16 MFMA path (index into the tile table of gemm.hip),
-// K split ksplit ways: for measurement; launch_gemm chooses for the forward.
-hipError_t launch_gemm_tile(Epilogue epi, const GemmParams& p, int tile, int ksplit, hipStream_t s);
-// Sum of ksplit fp32 partial slices in p.part and the epilogue (tile width bn,
-// for the SwiGLU column interleave).
-hipError_t launch_gemm_reduce(Epilogue epi, const GemmParams& p, int ksplit, int bn, hipStream_t s);
 
 // ---------------------------------------------------------------- read-out
 struct ClsParams {
