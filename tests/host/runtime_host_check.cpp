@@ -62,17 +62,28 @@ size_t dsize(DType t) { return t == kF32 ? 4 : 2; }
 
 namespace sp {
 
+// Norms offered to the projections before them, those taken, and the output of one
+// that was not: the next launch must be its RMSNorm.
+static long norms_offered = 0, norms_fused = 0;
+static const void* pending_norm = nullptr;
+
 hipError_t launch_rmsnorm_rows(DType in_dt, DType gain_dt, DType out_dt, const void* x, int64_t ld_x,
                                const void* gain, const void* gain2, void* out, int64_t ld_out, int rows, int d,
                                float eps, int* status, hipStream_t) {
   (void)gain_dt; (void)gain; (void)gain2; (void)eps;
   g.expect(rows >= 0 && d > 0 && d % 4 == 0 && d <= 16384, "rmsnorm shape");
+  g.expect(!pending_norm || pending_norm == out, "a norm left to the caller was not launched");
+  pending_norm = nullptr;
   if (rows <= 0) return hipSuccess;
   g.range(x, ((size_t)(rows - 1) * ld_x + d) * dsize(in_dt), "rmsnorm in");
   g.range(out, ((size_t)(rows - 1) * ld_out + d) * dsize(out_dt), "rmsnorm out");
   g.range(status, 4, "status");
   return hipSuccess;
 }
+
+// The list of the last RoPE launch that wrote one, which the attention after it reads.
+static const int2* listed_items = nullptr;
+static int listed_split_len = 0;
 
 hipError_t launch_rope_scatter(DType dt, const RopeParams& p, int batch, hipStream_t) {
   const size_t e = dsize(dt), hd = p.hd;
@@ -99,6 +110,19 @@ hipError_t launch_rope_scatter(DType dt, const RopeParams& p, int batch, hipStre
     g.range(p.k_soft_lo, ks, "rope k_soft_lo");
     g.range(p.v_soft_lo, vs, "rope v_soft_lo");
   }
+  // the work list it writes on the side: room for every split of every sequence
+  if (p.items) {
+    g.expect(dt == kBF16 && p.split_len > 0 && batch < 65535, "work list: of the bf16 path, split_len, grid rows");
+    const size_t splits = p.split_len > 0 && p.max_seq_len > p.split_len
+                              ? ((size_t)p.max_seq_len + p.split_len - 1) / p.split_len : 1;
+    g.range(p.items, (size_t)batch * splits * 8, "work list");
+    g.range(p.n_items, 4, "work-list length");
+  }
+  if (p.items || p.step == 0) {  // (later recursive steps run the first one's list)
+    listed_items = p.items;
+    listed_split_len = p.split_len;
+  }
+  if (p.clear_padding) g.expect(p.step == 0 && p.per_seq == 0, "padding cleared by the one-pass form");
   g.range(p.status, 4, "status");
   return hipSuccess;
 }
@@ -120,7 +144,9 @@ static void attn_common(const AttnParams& p, int hd, int batch, size_t e) {
   if (e == 2) g.range(p.q_lo, rows * hd * e, "attention q_lo");
   g.range(p.o_part, rows * p.max_splits * hd * e, "attention o_part");  // fp16 (bf16 path) or fp32
   g.range(p.ml_part, rows * p.max_splits * 8, "attention ml_part");
+  g.expect(p.items == listed_items, "attention work list: not the one written");
   if (p.items) {
+    g.expect(p.split_len == listed_split_len, "attention work list: of another split length");
     g.range(p.items, (size_t)batch * p.max_splits * 8, "attention work list");
     g.range(p.n_items, 4, "attention work-list length");
   }
@@ -131,16 +157,6 @@ hipError_t launch_attention_bf16(const AttnParams& p, int hd, int waves, int bat
            "attention tiles");
   g.expect(p.split_len % 32 == 0, "split_len multiple of the unit");
   attn_common(p, hd, batch, 2);
-  return hipSuccess;
-}
-
-hipError_t launch_work_list(const int* seq_lens, int batch, int max_seq_len, int split_len, int2* items, int* count,
-                            hipStream_t) {
-  (void)seq_lens;
-  g.expect(split_len > 0, "work list: split_len");
-  g.range(items, (size_t)batch * ((max_seq_len + split_len - 1) / split_len > 0 ? (max_seq_len + split_len - 1) / split_len : 1) * 8,
-          "work list");
-  g.range(count, 4, "work-list length");
   return hipSuccess;
 }
 
@@ -170,6 +186,8 @@ hipError_t launch_merge(DType dt, const MergeParams& p, int batch, hipStream_t) 
 
 hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p, hipStream_t) {
   if (p.M <= 0) return hipSuccess;
+  g.expect(!pending_norm, "a norm left to the caller was not launched");
+  pending_norm = nullptr;
   g.expect(!p.b_f16 || dt == kBF16, "fp16 image on an fp32 config");
   g.expect(p.N > 0 && p.K > 0 && p.lda >= p.K && p.ldb >= p.K, "gemm shape");
   const size_t ea = dt == kF32 ? 4 : 2;
@@ -186,6 +204,18 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p, hipStream_t)
   }
   if (epi == kEpiRowScale) g.range(p.r, (size_t)p.M * 4, "gemm row scales");
   g.range(p.part, p.part_bytes, "gemm split-K scratch");
+  auto al16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
+  g.expect(al16(p.a) && al16(p.c) && al16(p.part) && (epi == kEpiRowScale || al16(p.r)) && p.ldc % 4 == 0,
+           "gemm operands aligned");
+  if (p.norm_done) {
+    // the norm that follows: as launch_rmsnorm_rows would write it; in the
+    // reduction for every other product, so that both ways of the caller run
+    g.expect(dt == kBF16 && (epi == kEpiResidRow || epi == kEpiResidF32) && p.norm_gain && p.norm_ld >= p.N, "gemm norm");
+    g.range(p.norm_out, ((size_t)(p.M - 1) * p.norm_ld + p.N) * 2, "gemm norm out");
+    *p.norm_done = (++norms_offered & 1) != 0;
+    norms_fused += *p.norm_done;
+    if (!*p.norm_done) pending_norm = p.norm_out;
+  }
   g.range(p.status, 4, "status");
   g.expect(p.n_cus >= 1 && p.n_xcd >= 1, "gemm device shape");
   return hipSuccess;
@@ -403,6 +433,8 @@ int main(int argc, char** argv) {
                  SP_ERR_NO_DEVICE, "forward without allocation, no device");
     g.expect(sp_probe_pack_weights(&fixed[1].cfg, &wt, nullptr, 0, nullptr) == SP_ERR_INVALID_ARG, "pack arguments");
   }
+  g.where = "norms";
+  g.expect(sp::norms_fused > 0 && sp::norms_fused < sp::norms_offered, "both ways of a norm after a projection");
   std::printf("host runtime check: %ld checks, %d random configs accepted, %ld failures\n", g.checks, accepted,
               g.failures);
   return g.failures ? 1 : 0;
