@@ -1,0 +1,36 @@
+"""Projections with bf16 weights as stored against the same with the fp16 image, which
+differ by the conversion alone: the time of each product of a forward, over row
+counts at which other tiles are chosen."""
+import pytest
+import torch
+
+from paper_2608_28099_amd import binding, configs, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _products(w, image):
+    dev = torch.device("cuda:0")
+    kv, params = inputs.kv_cache(w, inputs.seq_lens(w), dev), inputs.params(w, dev)
+    if image:
+        params["packed"] = binding.pack_weights(w, params)
+    probe = binding.Probe(w, flags=binding.SP_FLAG_PROFILE)
+    for reps in (4, 12):
+        for _ in range(reps):
+            probe.forward(kv, params)
+        stages, n = probe.profile_read()
+    probe.close()
+    return {s: stages[s] / n for s in ("o_proj", "gate_up", "down")}
+
+
+# 256 x 160 tiles, whose eight waves each convert every column, made the gate/up
+# products 3.8 to 4.8 times those with the image; without them each product is at
+# most 2.6 times (where the image takes those tiles and the matrices as stored do not)
+@pytest.mark.parametrize("hidden,intermediate,batch", [(4096, 12288, 640), (2560, 9728, 400), (2560, 9728, 1024),
+                                                       (5120, 17408, 192), (5120, 17408, 257), (3072, 352, 896)])
+def test_the_conversion_is_not_multiplied(hidden, intermediate, batch):
+    w = configs.Workload(name="stored", dtype="bf16", batch=batch, k=1, hidden=hidden, n_q_heads=32, n_kv_heads=8,
+                         head_dim=128, intermediate=intermediate, n_classes=2, seq_len=("fixed", 16), seed=batch)
+    image, stored = _products(w, True), _products(w, False)
+    for s in stored:
+        assert stored[s] <= 3.1 * image[s], (s, stored, image)
