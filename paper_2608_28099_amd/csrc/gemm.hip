@@ -671,8 +671,7 @@ hipError_t launch_reduce_norm(const GemmParams& p, int ksplit, hipStream_t s) {
 }
 
 // What launch_gemm asks of a tile; the kernels of the rest are not built.
-// SwiGLU and the other epilogues, with K split or not; weights as the fp16 image only.
-enum : int { kGate = 1, kGateSplit = 2, kPlain = 4, kPlainSplit = 8, kImageOnly = 16 };
+enum : int { kGate = 1, kGateSplit = 2, kPlain = 4, kPlainSplit = 8 };  // SwiGLU, the other epilogues; with K split
 
 template <int BM, int BN, int WGM, int WGN, int S, int BK, int USE, bool ST, bool PART, bool WB>
 hipError_t launch_tile_k(Epilogue epi, const GemmParams& p, dim3 grid, hipStream_t s) {
@@ -703,18 +702,23 @@ hipError_t launch_tile_k(Epilogue epi, const GemmParams& p, dim3 grid, hipStream
 hipError_t launch_gemm_reduce(Epilogue epi, const GemmParams& p, int ksplit, int bn, hipStream_t s);
 
 // K split ksplit ways (ksplit > 1: fp32 partials in p.part, then the reduction).
-template <int BM, int BN, int WGM, int WGN, int S, int BK, int USE, bool ST = false>
+// BM_WAVES x BN_WAVES: the waves of a workgroup for weights as stored.  Each wave
+// converts the columns it holds, so where BN_WAVES is 1 all WGM waves of a tile convert
+// all of its columns: 192 rows of 34816 x 5120 in 256 x 160 tiles took 491 us in 8 x 1
+// waves and 109 in 2 x 5 (fp16 image, 8 x 1: 112); 128 x 160, 128 rows of 24576 x 4096, 80.6 and
+// 58.2; 64 x 160, 58.7 and 46.0 on 33 rows; 128 x 96, 52.1 and 47.3.  The fp16 image is as
+// fast or faster in the first layout.  Every output is the same sum in either.
+template <int BM, int BN, int WGM, int WGN, int S, int BK, int USE, bool ST = false, int BM_WAVES = WGM, int BN_WAVES = WGN>
 hipError_t launch_tile(Epilogue epi, const GemmParams& p, int ksplit, hipStream_t s) {
   if (p.K % BK || p.K / BK < ksplit) return hipErrorInvalidValue;  // slices of whole steps, maybe uneven
-  constexpr int USE_BF16 = (USE & kImageOnly) != 0 ? 0 : USE;
   const dim3 grid(((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN), ksplit);
   hipError_t e;
   if (ksplit > 1)
     e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, USE, ST, true, false>(epi, p, grid, s)
-                : launch_tile_k<BM, BN, WGM, WGN, S, BK, USE_BF16, ST, true, true>(epi, p, grid, s);
+                : launch_tile_k<BM, BN, BM_WAVES, BN_WAVES, S, BK, USE, ST, true, true>(epi, p, grid, s);
   else
     e = p.b_f16 ? launch_tile_k<BM, BN, WGM, WGN, S, BK, USE, ST, false, false>(epi, p, grid, s)
-                : launch_tile_k<BM, BN, WGM, WGN, S, BK, USE_BF16, ST, false, true>(epi, p, grid, s);
+                : launch_tile_k<BM, BN, BM_WAVES, BN_WAVES, S, BK, USE, ST, false, true>(epi, p, grid, s);
   if (e != hipSuccess || ksplit == 1) return e;
   return launch_gemm_reduce(epi, p, ksplit, BN, s);
 }
@@ -745,8 +749,8 @@ constexpr TileShape kTiles[kNumTiles] = {
     {16, 32, 1, 1, 32},   {32, 128, 1, 4, 64},  {256, 256, 4, 2, 64}, {256, 160, 4, 2, 64},
     {256, 192, 4, 2, 64}, {256, 160, 8, 1, 64},
     {16, 64, 1, 4, 64},   {16, 96, 1, 3, 64},   {16, 160, 1, 5, 64},  {32, 96, 2, 1, 64},  {32, 160, 1, 5, 64},
-    {64, 64, 4, 1, 64},   {64, 96, 4, 1, 64},   {64, 128, 4, 1, 64},  {64, 160, 4, 1, 64}, {128, 96, 4, 1, 64},
-    {128, 128, 4, 2, 64}, {128, 160, 4, 1, 64}, {32, 128, 1, 4, 64},  {128, 64, 4, 2, 64}};
+    {64, 64, 2, 2, 64},   {64, 96, 4, 1, 64},   {64, 128, 2, 4, 64},  {64, 160, 4, 1, 64}, {128, 96, 4, 1, 64},
+    {128, 128, 2, 4, 64}, {128, 160, 4, 1, 64}, {32, 128, 1, 4, 64},  {128, 64, 4, 2, 64}};
 constexpr int kOrderSwiglu[9] = {0, 1, 2, 3, 4, 5, 6, 7, 8};
 constexpr int kOrderResid[9] = {2, 1, 0, 3, 4, 5, 6, 7, 8};
 
@@ -772,19 +776,19 @@ hipError_t launch_tile_index(int c, Epilogue epi, const GemmParams& p, int kspli
     case 10: return launch_tile<256, 256, 4, 2, 2, 64, kPlain | kPlainSplit | kGate>(epi, p, ksplit, s);
     case 11: return launch_tile<256, 160, 4, 2, 3, 64, kPlain>(epi, p, ksplit, s);
     case 12: return launch_tile<256, 192, 4, 2, 2, 64, kGate>(epi, p, ksplit, s);
-    case 13: return launch_tile<256, 160, 8, 1, 3, 64, kGate | kImageOnly, true>(epi, p, ksplit, s);
+    case 13: return launch_tile<256, 160, 8, 1, 3, 64, kGate, true, 2, 5>(epi, p, ksplit, s);
     case 14: return launch_tile<16, 64, 1, 4, 14, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
     case 15: return launch_tile<16, 96, 1, 3, 10, 64, kGate, true>(epi, p, ksplit, s);
     case 16: return launch_tile<16, 160, 1, 5, 7, 64, kGate, true>(epi, p, ksplit, s);
-    case 17: return launch_tile<32, 96, 2, 1, 8, 64, kGate, true>(epi, p, ksplit, s);
+    case 17: return launch_tile<32, 96, 2, 1, 8, 64, kGate, true, 1, 3>(epi, p, ksplit, s);
     case 18: return launch_tile<32, 160, 1, 5, 6, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
-    case 19: return launch_tile<64, 64, 4, 1, 8, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
-    case 20: return launch_tile<64, 96, 4, 1, 7, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
-    case 21: return launch_tile<64, 128, 4, 1, 6, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
-    case 22: return launch_tile<64, 160, 4, 1, 5, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
-    case 23: return launch_tile<128, 96, 4, 1, 5, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
-    case 24: return launch_tile<128, 128, 4, 2, 5, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
-    case 25: return launch_tile<128, 160, 4, 1, 4, 64, kPlain | kPlainSplit | kGate, true>(epi, p, ksplit, s);
+    case 19: return launch_tile<64, 64, 2, 2, 8, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 20: return launch_tile<64, 96, 4, 1, 7, 64, kPlain | kPlainSplit | kGate, true, 1, 3>(epi, p, ksplit, s);
+    case 21: return launch_tile<64, 128, 2, 4, 6, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 22: return launch_tile<64, 160, 4, 1, 5, 64, kPlain | kPlainSplit | kGate, true, 2, 5>(epi, p, ksplit, s);
+    case 23: return launch_tile<128, 96, 4, 1, 5, 64, kPlain | kPlainSplit | kGate, true, 2, 3>(epi, p, ksplit, s);
+    case 24: return launch_tile<128, 128, 2, 4, 5, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
+    case 25: return launch_tile<128, 160, 4, 1, 4, 64, kPlain | kPlainSplit | kGate, true, 2, 5>(epi, p, ksplit, s);
     case 26: return launch_tile<32, 128, 1, 4, 6, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
     case 27: return launch_tile<128, 64, 4, 2, 6, 64, kPlain | kPlainSplit, true>(epi, p, ksplit, s);
   }
@@ -1003,7 +1007,7 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
       const TileShape& t = kTiles[cand[i]];
       if (!tile_ok(p, epi, t)) continue;
       const long tiles = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
-      if (cand[i] == kRaggedWide && (!p.b_f16 || 2 * tiles < cus)) continue;
+      if (cand[i] == kRaggedWide && 2 * tiles < cus) continue;
       const double cost = (double)((tiles + cus - 1) / cus) * t.bm * t.bn / rate[i];
       if (best < 0 || cost < best_cost) { best = cand[i]; best_cost = cost; }
     }
@@ -1015,11 +1019,9 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // 1024 x 19456 x 2560 this takes 256 x 128 (608 tiles, 0.140 ms) over
   // 256 x 256 (304 tiles: two rounds, the second nearly empty, 0.154 ms); at
   // 256 x 34816 x 5120 (last-row-only rows of the 27B shape) 256 x 160 in one round
-  // of 218 tiles (112 us) over 136 of 256 x 256 (140 us).  Not 256 x 160 with weights as
-  // stored: its waves hold all 160 columns each, and each of the eight
-  // converts them (640 x 24576 x 4096: 724 us, 223 with the choice below; 257 x 34816
-  // x 5120: 825 and 347); nor where its grid leaves half the compute units idle, on
-  // widths that no other wide tile divides (896 x 704 x 3072: 50 us, 27).
+  // of 218 tiles (112 us) over 136 of 256 x 256 (140 us).  Not 256 x 160 where its
+  // grid leaves half the compute units idle, on widths that no other wide tile
+  // divides (896 x 704 x 3072: 50 us, 27 in 64 x 64).
   const long tiles2 = (long)((p.M + 255) / 256) * (p.N / 128);
   if (epi == kEpiSwiglu && (p.M > 256 || (p.M >= 128 && 2 * tiles2 >= cus))) {
     static const int cand[5] = {10, 0, 2, 12, 13};

@@ -2,6 +2,8 @@
 // forward can ask for, with kernel launches replaced by a recorder, and
 //  - answers every one of them (no plan names a kernel that is not built),
 //  - covers the output with tiles and keeps the K slices inside the scratch,
+//  - takes the same tiles, K slices and order for weights as stored and as the fp16
+//    image (the waves of a tile may lie differently), so that results are the same,
 //  - prints the kernels it chose, one per line, for comparison with those the
 //    library holds.
 // With arguments "M N K epilogue part_bytes" it prints the launches of that one
@@ -36,6 +38,25 @@ std::string kernel_name() {  // "kernel<...>" out of "...Tag<&(sp::(anonymous na
   std::free(d);
   const size_t at = s.rfind("gemm_"), end = s.find('(', at);
   return at == std::string::npos || end == std::string::npos ? s : s.substr(at, end - at);
+}
+
+// What decides the order of a launch's sums: the kernel without its wave layout and kind of weights, the grid.
+std::string sums_of(const Launch& l) {
+  std::vector<std::string> args;
+  const size_t open = l.kernel.find('<');
+  std::string s = l.kernel.substr(0, open), cur;
+  for (size_t i = open + 1; open != std::string::npos && i < l.kernel.size(); ++i) {
+    const char c = l.kernel[i];
+    if (c == ',' || c == '>') { args.push_back(cur); cur.clear(); }
+    else if (c != ' ') cur += c;
+  }
+  const bool lds = s == "gemm_lds", rows = s == "gemm_rows";
+  for (size_t i = 0; i < args.size(); ++i) {
+    if (lds && (i == 2 || i == 3)) continue;
+    if ((lds || rows) && i + 1 == args.size()) continue;
+    s += "," + args[i];
+  }
+  return s + " " + std::to_string(l.grid.x) + " " + std::to_string(l.grid.y) + ";";
 }
 
 template <auto F>
@@ -96,7 +117,8 @@ int main(int argc, char** argv) {
     for (int e = 0; e <= (int)kEpiRowScale; ++e)
       for (int m : rows)
         for (int n : widths)
-          for (int k : depths)
+          for (int k : depths) {
+            std::string sums[2];
             for (int image = 0; image < 2; ++image) {
               const Epilogue epi = (Epilogue)e;
               if (epi == kEpiSwiglu && n % 64) continue;
@@ -141,8 +163,11 @@ int main(int argc, char** argv) {
                   }
                 }
                 if (outputs < (int64_t)m * n) fail("outputs left out", epi, p);
+                for (const Launch& l : g_launches) sums[image] += sums_of(l);
               }
+              if (image && sums[0] != sums[1]) fail("other sums with the image", epi, p);
             }
+          }
   // fp32: rows past one grid dimension among them
   for (int e = 0; e <= (int)kEpiRowScale; ++e)
     for (int m : {1, 16, 17, 64, 4096, 16 * 65535, 16 * 65535 + 1, 64 * 65535 + 1})

@@ -23,9 +23,9 @@ def _products(w, image):
     return {s: stages[s] / n for s in ("o_proj", "gate_up", "down")}
 
 
-# 256 x 160 tiles, whose eight waves each convert every column, made the gate/up
-# products 3.8 to 4.8 times those with the image; without them each product is at
-# most 2.6 times (where the image takes those tiles and the matrices as stored do not)
+# With one wave of columns per tile all the waves convert every column: gate/up took 3.8
+# to 4.9 times as long as with the image.  In layouts that convert each column once or
+# twice no product here takes more than 1.4 times as long.
 @pytest.mark.parametrize("hidden,intermediate,batch", [(4096, 12288, 640), (2560, 9728, 400), (2560, 9728, 1024),
                                                        (5120, 17408, 192), (5120, 17408, 257), (3072, 352, 896)])
 def test_the_conversion_is_not_multiplied(hidden, intermediate, batch):
@@ -33,4 +33,4 @@ def test_the_conversion_is_not_multiplied(hidden, intermediate, batch):
                          head_dim=128, intermediate=intermediate, n_classes=2, seq_len=("fixed", 16), seed=batch)
     image, stored = _products(w, True), _products(w, False)
     for s in stored:
-        assert stored[s] <= 3.1 * image[s], (s, stored, image)
+        assert stored[s] <= 1.8 * image[s], (s, stored, image)
