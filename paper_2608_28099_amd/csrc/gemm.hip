@@ -878,7 +878,8 @@ static int whole_round_columns(const GemmParams& p, int cus, double other, doubl
 // 70.0, 37.1 -> 25.7, 58.3 -> 40.0, 27.3 -> 26.8, 23.1 -> 17.3; 16 rows: SwiGLU 42.6 ->
 // 33.6, 97.9 -> 65.1, 29.3 -> 21.5; 256 rows: 4096 x 4096 26.2 -> 22.4, 4096 x 12288
 // 52.4 -> 43.0, 2560 x 9728 42.1 -> 28.8.  Returns the tile, or -1 where no choice fills
-// half the compute units (narrow heads: the smaller tiles below).
+// half the compute units (narrow heads: the smaller tiles below).  A slice has at least
+// six steps (128 rows of 3072 x 2048 in eight of four: 13.9 us, in four 12.5).
 static int stream_choice(Epilogue epi, const GemmParams& p, int cus, int* ksplit) {
   static constexpr int kBy16[] = {14}, kBy32[] = {26, 18}, kBy64[] = {19, 20, 21, 22}, kBy128[] = {27, 23, 24, 25};
   static constexpr int kGate16[] = {15, 16}, kGate32[] = {17, 18}, kGate64[] = {20, 22}, kGate128[] = {23, 25};
@@ -894,7 +895,7 @@ static int stream_choice(Epilogue epi, const GemmParams& p, int cus, int* ksplit
     const long tiles = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
     const int KT = p.K / t.bk;
     for (int ks = 1; ks <= (gate ? 1 : 8); ++ks) {
-      if (ks > 1 && (tiles * ks > cus || KT < 4 * ks || !p.part ||
+      if (ks > 1 && (tiles * ks > cus || KT < 6 * ks || !p.part ||
                      (size_t)ks * p.M * p.N * sizeof(float) > p.part_bytes))
         break;
       if (2 * tiles * ks < cus) continue;
@@ -907,61 +908,63 @@ static int stream_choice(Epilogue epi, const GemmParams& p, int cus, int* ksplit
   return best;
 }
 
-hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t s) {
-  if (p0.M <= 0) return hipSuccess;
-  if (dt == kF32) {
-    switch (epi) {
-      case kEpiStore: return launch_f32<kEpiStore>(p0, s);
-      case kEpiResidRow: return launch_f32<kEpiResidRow>(p0, s);
-      case kEpiResidF32: return launch_f32<kEpiResidF32>(p0, s);
-      case kEpiRowScale: return launch_f32<kEpiRowScale>(p0, s);
-      case kEpiSwiglu: return launch_f32<kEpiSwiglu>(p0, s);
-    }
-    return hipErrorInvalidValue;
+// Price of a plan for at most 256 rows, in us: a tile's steps per round of workgroups,
+// the weights' bytes and a constant, fitted per tile to every plan of 4680 products (4
+// to 256 rows of 180 matrices, weights as stored and as the fp16 image) with a spread
+// of 9 percent; the reduction of a split by slices and partial sums; gemm_rows (tile
+// kRows) by depth and workgroups per compute unit.  One price for both kinds of weights:
+// the plan, and with it the order of every sum, must not depend on the kind.
+// The shapes of the streaming tiles (stream_choice) follow the heads they were tuned on;
+// against the plans of any number of rows this decides.  Without it 269 of those
+// products were over a tenth slower than on the latter (128 rows of 3072 x 1024: 11.4 us
+// against 6.6), now 10, by up to a fifth.  Negative: not priced.
+constexpr int kRows = -1;
+constexpr double kNormLaunch = 1.5;  // what a norm of its own costs over one in a split's reduction
+struct PlanCost { double step, mb, fixed; };
+constexpr PlanCost kTileCost[kNumTiles] = {
+    {}, {}, {0.752, 0.035, 3.98}, {0.313, 0.067, 4.27}, {0.216, 0.087, 3.99}, {0.205, 0.071, 4.23},
+    {0.178, 0.200, 3.45}, {0.135, 0.200, 3.15}, {}, {0.222, 0.125, 3.55}, {1.536, 0.081, 5.57}, {}, {}, {},
+    {0.126, 0.103, 4.76}, {0.205, 0.086, 4.63}, {0.362, 0.079, 4.24}, {0.255, 0.072, 4.74}, {0.394, 0.070, 4.24},
+    {0.197, 0.091, 4.32}, {0.319, 0.062, 4.55}, {0.371, 0.064, 4.13}, {0.489, 0.052, 4.34}, {0.475, 0.036, 4.79},
+    {0.502, 0.042, 4.49}, {0.666, 0.021, 4.92}, {0.291, 0.081, 3.89}, {0.319, 0.076, 4.31}};
+
+static double plan_price(Epilogue epi, const GemmParams& p, int cus, int tile, int ks) {
+  const bool gate = epi == kEpiSwiglu;
+  const double mb = 2e-6 * p.N * p.K, norm = p.norm_done ? kNormLaunch : 0.0;
+  if (tile == kRows) {
+    const long wgs = (long)(p.N / (gate ? 32 : 16)) * ((p.M + 15) / 16);
+    const double depth = p.K / 1024.0 * (double)((wgs + cus - 1) / cus);
+    if (gate) return p.M <= 8 ? 2.02 * depth + 0.061 * mb + 2.3 : 2.65 * depth + 0.043 * mb + 2.2;
+    return norm + (p.M <= 8 ? 1.10 * depth + 0.056 * mb + 2.6 : 1.63 * depth + 0.028 * mb + 2.7);
   }
-  if (p0.K % 32 || p0.lda % 8 || p0.ldb % 8) return hipErrorInvalidValue;
-  GemmParams p = p0;
-  const int cus = p.n_cus > 0 ? p.n_cus : 256;
-  if (p.n_xcd < 1) p.n_xcd = 1;
-  // group of row tiles: the XCD's compute units then cover about a square of
-  // tiles (8 row tiles by 4 column tiles with 32 compute units per XCD)
-  if (p.group_m < 1) p.group_m = 8;
+  const PlanCost& c = kTileCost[tile];
+  if (c.step == 0.0) return -1.0;
+  const TileShape& t = kTiles[tile];
+  const long wgs = (long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn) * ks;
+  const int steps = (p.K / t.bk + ks - 1) / ks;
+  const double rounds = (double)((wgs + cus - 1) / cus);
+  double us = c.step * steps * rounds + c.mb * mb + c.fixed;
+  // one-wave tiles, several to a compute unit: a wave's chain of steps, or the weights'
+  // bytes, read again by each row tile (partly from the L2)
+  if (t.wgm * t.wgn == 1)
+    us = std::max(c.step * steps, c.mb * mb * std::max(1.0, 0.4 * ((p.M + t.bm - 1) / t.bm))) + c.fixed;
+  // streaming tiles that leave compute units idle have fewer loads in flight (64 rows of
+  // 16384 x 3072, 171 workgroups: 28.3 us against 22.1 for 256 of 64 x 64)
+  if (gate && tile >= kStreamTiles && p.M > 32 && wgs < cus) us *= 1.0 + 0.3 * (1.0 - (double)wgs / cus);
+  const double part_mb = 4e-6 * ks * p.M * p.N;
+  if (ks > 1) return us + (gate ? 0.90 + 0.31 * ks + 0.63 * part_mb : 0.93 + 0.28 * ks + 0.41 * part_mb);
+  // unsplit, the epilogue reads the residuals one by one
+  const double outs = (double)t.bm * t.bn / (64 * t.wgm * t.wgn) * rounds;
+  return us + norm + (gate || epi == kEpiStore ? 0.0 : 0.04 * outs);
+}
+
+// A plan: the tile, its K slices, and (first > 0) the leading 256-column tiles that go to
+// tile 10 in a launch before it.
+struct TilePlan { int tile, ksplit, first; };
+
+// The plan on the tiles that serve any number of rows.
+static TilePlan tile_plan(Epilogue epi, const GemmParams& p, int cus) {
   auto fits = [&](int ks) { return p.part && (size_t)ks * p.M * p.N * sizeof(float) <= p.part_bytes; };
-  // The streaming tiles.  SwiGLU: up to 128 rows.  Up to 16 rows, the other
-  // epilogues: long K of matrices wider than gemm_rows takes (5120 x 17408: 37 us
-  // against 44 for the one-wave tiles; 6144 x 4096 stays there, 12.9 us against 15.7),
-  // and from 13 rows and K = 9216 those it would take (16 rows: 2560 x 9728 21.7 -> 17.5
-  // us, 4096 x 12288 27.2 -> 24.8; at 9 rows 18.4 -> 17.2 and 23.7 -> 24.6; 13 rows of 4096 x
-  // 8192: 17.6 against 18.7).  17-128 rows, unless
-  // gemm_rows below covers them with a workgroup per compute unit.  129-256 rows: K
-  // of 4096 or more, not the QKV product (7168 x 5120: 37.7 us on the plan below, 39.0).
-  const int rows_cols = epi == kEpiSwiglu ? 32 : 16;
-  const bool rows_fit = (int64_t)(p.N / rows_cols) * ((p.M + 15) / 16) <= cus;
-  const bool stream = epi == kEpiSwiglu ? p.M <= 128 && !(p.M > 16 && rows_fit)
-                      : p.M <= 16       ? (rows_fit ? p.M > 12 && p.K >= 9216 : p.K >= 8192)
-                      : p.M <= 128      ? !rows_fit
-                                        : p.M <= 256 && p.K >= 4096 && epi != kEpiStore;
-  if (stream) {
-    int ks = 1;
-    const int t = stream_choice(epi, p, cus, &ks);
-    if (t >= 0) {
-      return launch_tile_index(t, epi, p, ks, s);
-    }
-  }
-  // gemm_rows: at most one workgroup per compute unit (16 rows of matrices up to
-  // 4096 wide, more rows of narrower ones), and the SwiGLU of up to 16 rows that the
-  // streaming tiles leave.  Wider
-  // products on few rows keep the one-wave tiles below: their tiles do not divide
-  // evenly over the compute units either way, and one wave each balances better
-  // (5 rows: 6144 x 4096 12.5 us against 13.5).  More rows of narrow matrices leave
-  // most compute units idle, so past K = 4096 the plans below split K over
-  // workgroups too (32 rows of 1024 x 4096: 9.9 us here, 10.3 in eight slices; 512 x 8192
-  // 16.7 and 10.8; 1024 x 28672 52.2 and 24.5; 64 rows of it 52.2 and 28.2).
-  const bool split_narrow = epi != kEpiSwiglu && p.M > 16 && p.M <= 128 && p.K > 4096 &&
-                            tile_ok(p, epi, kTiles[p.M <= 32 ? 9 : 3]) && fits(8);
-  if (((epi == kEpiSwiglu && p.M <= 16) || (rows_fit && !split_narrow)) && p.N % rows_cols == 0 &&
-      (epi == kEpiSwiglu || (p.b_split0 % 16 == 0 && p.b_split1 % 16 == 0)))
-    return launch_gemm_rows(epi, p, s);
   // 17..32 rows of what the streaming tiles leave: a 32-row by 128-column tile
   // with four waves, and K split so that the grid has enough workgroups in
   // flight (each slice at least 8 steps of 64).  (Up to 16 rows the one-wave
@@ -970,7 +973,7 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
     const int tiles = p.N / 128, KT = p.K / 64;
     int ks = 1;
     while (ks < 16 && tiles * ks * 2 <= 4 * cus && KT / (ks * 2) >= 8 && fits(ks * 2)) ks *= 2;
-    return launch_tile_index(9, epi, p, ks, s);
+    return {9, ks, 0};
   }
   // K of 4096 or more with a few hundred rows (o and down on 129-1024 rows):
   // 256 x 128 tiles with K split re-read the activations and weights half as
@@ -985,7 +988,7 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   if (epi != kEpiSwiglu && p.M > 128 && p.M <= 1024 && p.K >= 4096 && tile_ok(p, epi, kTiles[2])) {
     const long tiles = (long)((p.M + 255) / 256) * (p.N / 128);
     const int ks = (int)std::min<long>(p.M > 256 && p.K >= 8192 ? 6 : 4, std::max<long>(2, cus / tiles));
-    if (p.K % 64 == 0 && p.K / 64 >= 8 * ks && fits(ks)) return launch_tile_index(2, epi, p, ks, s);
+    if (p.K % 64 == 0 && p.K / 64 >= 8 * ks && fits(ks)) return {2, ks, 0};
   }
   // 33..256 rows of the other epilogues that the streaming tiles leave (QKV on more
   // than 128 rows, K under 4096 there, narrow matrices): 128 x 64 tiles with K split
@@ -995,7 +998,7 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
     const long tiles = (long)((p.M + 127) / 128) * (p.N / 64);
     int ks = 2;
     while (ks < 8 && tiles * ks < cus) ks *= 2;
-    if (p.K / 64 / ks >= 8 && fits(ks)) return launch_tile_index(3, epi, p, ks, s);
+    if (p.K / 64 / ks >= 8 && fits(ks)) return {3, ks, 0};
   }
   // The wide tiles, priced by the rounds of workgroups the grid takes on the
   // compute units (a last partial round costs a whole one) times the tile's
@@ -1034,14 +1037,9 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
       const long tb_tiles = (long)((p.M + tb.bm - 1) / tb.bm) * ((p.N + tb.bn - 1) / tb.bn);
       const int bi = best == 10 ? 0 : best == 0 ? 1 : best == 2 ? 2 : best == 12 ? 3 : 4;
       const int na = whole_round_columns(p, cus, (double)((tb_tiles + cus - 1) / cus) * tb.bm * tb.bn / rate[bi], 0.87);
-      if (na > 0) {
-        GemmParams qa = p;
-        qa.N = 256 * na;
-        const hipError_t e = launch_tile_index(10, epi, qa, 1, s);
-        return e != hipSuccess ? e : launch_tile_index(2, epi, columns_from(p, epi, 256 * na), 1, s);
-      }
+      if (na > 0) return {2, 1, na};
     }
-    if (best >= 0) return launch_tile_index(best, epi, p, 1, s);
+    if (best >= 0) return {best, 1, 0};
   }
   // Residual products on more than 1024 rows whose 256 x 128 grid fills the
   // compute units: 8192 x 5120 takes 256 x 160 (four whole rounds; o 0.408 ms,
@@ -1053,7 +1051,7 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
   // split measured slower).
   if (epi != kEpiSwiglu && p.M > 1024 && p.K >= 8192 && tile_ok(p, epi, kTiles[10]) &&
       2 * (long)((p.M + 255) / 256) * (p.N / 256) <= cus && p.K % 128 == 0 && fits(2))
-    return launch_tile_index(10, epi, p, 2, s);
+    return {10, 2, 0};
   // The mixed plan above applies here too (single weight block): 8192 x 5120
   // as two rounds of 256 x 256 over 4096 columns and one of 256 x 128 over the
   // last 1024 (down 1.22 ms, o 0.369 ms, against 1.34 and 0.389 for 256 x 160).
@@ -1067,14 +1065,9 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
       const long tb_tiles = (long)((p.M + tb.bm - 1) / tb.bm) * ((p.N + tb.bn - 1) / tb.bn);
       const int bi = best == 10 ? 0 : best == 11 ? 1 : 2;
       const int na = whole_round_columns(p, cus, (double)((tb_tiles + cus - 1) / cus) * tb.bm * tb.bn / rate[bi], 0.80);
-      if (na > 0) {
-        GemmParams qa = p;
-        qa.N = qa.b_split0 = qa.b_split1 = 256 * na;
-        const hipError_t e = launch_tile_index(10, epi, qa, 1, s);
-        return e != hipSuccess ? e : launch_tile_index(2, epi, columns_from(p, epi, 256 * na), 1, s);
-      }
+      if (na > 0) return {2, 1, na};
     }
-    if (best >= 0) return launch_tile_index(best, epi, p, 1, s);
+    if (best >= 0) return {best, 1, 0};
   }
   // First tile (in preference order) that gives at least one workgroup per
   // compute unit, else the valid tile with the most workgroups.
@@ -1088,7 +1081,77 @@ hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t
     if (tiles >= cus) { best = c; break; }
     if (tiles > best_tiles) { best_tiles = tiles; best = c; }
   }
-  return launch_tile_index(best, epi, p, 1, s);
+  return {best, 1, 0};
+}
+
+hipError_t launch_gemm(DType dt, Epilogue epi, const GemmParams& p0, hipStream_t s) {
+  if (p0.M <= 0) return hipSuccess;
+  if (dt == kF32) {
+    switch (epi) {
+      case kEpiStore: return launch_f32<kEpiStore>(p0, s);
+      case kEpiResidRow: return launch_f32<kEpiResidRow>(p0, s);
+      case kEpiResidF32: return launch_f32<kEpiResidF32>(p0, s);
+      case kEpiRowScale: return launch_f32<kEpiRowScale>(p0, s);
+      case kEpiSwiglu: return launch_f32<kEpiSwiglu>(p0, s);
+    }
+    return hipErrorInvalidValue;
+  }
+  if (p0.K % 32 || p0.lda % 8 || p0.ldb % 8) return hipErrorInvalidValue;
+  GemmParams p = p0;
+  const int cus = p.n_cus > 0 ? p.n_cus : 256;
+  if (p.n_xcd < 1) p.n_xcd = 1;
+  // group of row tiles: the XCD's compute units then cover about a square of
+  // tiles (8 row tiles by 4 column tiles with 32 compute units per XCD)
+  if (p.group_m < 1) p.group_m = 8;
+  const TilePlan tp = tile_plan(epi, p, cus);
+  // Up to 256 rows, the streaming tiles or gemm_rows instead, unless the plan above
+  // prices clearly cheaper (3%).  The streaming tiles serve SwiGLU up to 128 rows; up to 16 rows, the other
+  // epilogues: long K of matrices wider than gemm_rows takes (5120 x 17408: 37 us
+  // against 44 for the one-wave tiles; 6144 x 4096 stays there, 12.9 us against 15.7),
+  // and from 13 rows and K = 9216 those it would take (16 rows: 2560 x 9728 21.7 -> 17.5
+  // us, 4096 x 12288 27.2 -> 24.8; at 9 rows 18.4 -> 17.2 and 23.7 -> 24.6; 13 rows of 4096 x
+  // 8192: 17.6 against 18.7).  17-128 rows, unless
+  // gemm_rows covers them with a workgroup per compute unit.  129-256 rows: K
+  // of 4096 or more, not the QKV product (7168 x 5120: 37.7 us on the plan above, 39.0).
+  const int rows_cols = epi == kEpiSwiglu ? 32 : 16;
+  const bool rows_fit = (int64_t)(p.N / rows_cols) * ((p.M + 15) / 16) <= cus;
+  const bool stream = epi == kEpiSwiglu ? p.M <= 128 && !(p.M > 16 && rows_fit)
+                      : p.M <= 16       ? (rows_fit ? p.M > 12 && p.K >= 9216 : p.K >= 8192)
+                      : p.M <= 128      ? !rows_fit
+                                        : p.M <= 256 && p.K >= 4096 && epi != kEpiStore;
+  auto dearer = [&](int tile, int ks) {  // than the plan above
+    if (tp.first) return false;
+    const double mine = plan_price(epi, p, cus, tile, ks), other = tp.tile < 0 ? -1.0 : plan_price(epi, p, cus, tp.tile, tp.ksplit);
+    return mine >= 0.0 && other >= 0.0 && other < 0.97 * mine;
+  };
+  if (stream) {
+    int ks = 1;
+    const int t = stream_choice(epi, p, cus, &ks);
+    if (t >= 0) {
+      if (dearer(t, ks)) return launch_tile_index(tp.tile, epi, p, tp.ksplit, s);
+      return launch_tile_index(t, epi, p, ks, s);
+    }
+  }
+  // gemm_rows: at most one workgroup per compute unit (16 rows of matrices up to
+  // 4096 wide, more rows of narrower ones), and the SwiGLU of up to 16 rows that the
+  // streaming tiles leave.  Wider
+  // products on few rows keep the one-wave tiles: their tiles do not divide
+  // evenly over the compute units either way, and one wave each balances better
+  // (5 rows: 6144 x 4096 12.5 us against 13.5).  Long K of narrow matrices leaves most
+  // compute units idle here and is split over workgroups by its price (32 rows of 1024 x
+  // 4096: 9.9 us here, 10.3 in eight slices; 512 x 8192 16.7 and 10.8; 1024 x 28672
+  // 52.2 and 24.5).
+  if (((epi == kEpiSwiglu && p.M <= 16) || rows_fit) && p.N % rows_cols == 0 &&
+      (epi == kEpiSwiglu || (p.b_split0 % 16 == 0 && p.b_split1 % 16 == 0)) && !dearer(kRows, 1))
+    return launch_gemm_rows(epi, p, s);
+  if (tp.first) {
+    GemmParams q = p;
+    q.N = 256 * tp.first;
+    if (epi != kEpiSwiglu) q.b_split0 = q.b_split1 = q.N;
+    const hipError_t e = launch_tile_index(10, epi, q, 1, s);
+    return e != hipSuccess ? e : launch_tile_index(tp.tile, epi, columns_from(p, epi, q.N), 1, s);
+  }
+  return launch_tile_index(tp.tile, epi, p, tp.ksplit, s);
 }
 
 }  // namespace sp

@@ -7,8 +7,8 @@
 //  - prints the kernels it chose, one per line, for comparison with those the
 //    library holds.
 // With arguments "M N K epilogue part_bytes" it prints the launches of that one
-// residual product and the norm after it, on fp16 weights and 256 compute units:
-// kernel, grid x, y, z.
+// product (a residual one with the norm after it) on fp16 weights and 256 compute
+// units: kernel, grid x, y, z.
 #include "../../paper_2608_28099_amd/csrc/common.h"
 
 #include <cxxabi.h>
@@ -88,8 +88,10 @@ int main(int argc, char** argv) {
     p.b_split0 = p.b_split1 = p.N;
     p.b_f16 = 1; p.n_cus = 256; p.n_xcd = 8;
     p.part_bytes = std::strtoull(argv[5], nullptr, 10);
-    p.norm_done = &done;
-    if (launch_gemm(kBF16, (Epilogue)std::atoi(argv[4]), p, nullptr) != hipSuccess) return 1;
+    const int epi = std::atoi(argv[4]);
+    if (epi == kEpiResidRow || epi == kEpiResidF32) p.norm_done = &done;
+    if (epi == kEpiSwiglu) p.ldc = p.N / 2;
+    if (launch_gemm(kBF16, (Epilogue)epi, p, nullptr) != hipSuccess) return 1;
     for (const Launch& l : g_launches) std::printf("%s|%u|%u|%u\n", l.kernel.c_str(), l.grid.x, l.grid.y, l.grid.z);
     return 0;
   }

@@ -70,3 +70,30 @@ def test_the_norm_runs_in_the_reduction(check, hidden, batch, intermediate, o, f
             else:
                 assert [x[0].split("<")[0] for x in launches] == ["gemm_lds", "gemm_reduce_norm"], launches
                 assert int(launches[0][2]) == slices, launches
+
+
+STORE, RESID_F32, SWIGLU = 0, 2, 3
+# rows, width, depth, epilogue; us of plans (tile / K slices, or the row kernel), fp16
+# image.  Off the heads the streaming tiles were tuned on, then on them
+MEASURED = [
+    (65, 16384, 3072, SWIGLU, {"128x64/1": 23.1, "128x96/1": 29.7, "64x64/1": 30.1}),
+    (33, 16384, 1024, SWIGLU, {"64x64/1": 9.2, "128x64/1": 9.4, "64x96/1": 11.3}),
+    (17, 1536, 6144, SWIGLU, {"32x128/8": 10.9, "rows": 18.2}),
+    (12, 9728, 3072, SWIGLU, {"16x32/1": 14.8, "16x96/1": 18.2, "rows": 20.2}),
+    (128, 3072, 1024, STORE, {"16x32/1": 6.6, "64x64/1": 6.9, "128x64/4": 11.4}),
+    (33, 2048, 1024, STORE, {"16x16/1": 5.0, "rows": 5.2, "64x64/4": 8.1}),
+    (64, 24576, 4096, SWIGLU, {"64x96/1": 34.8, "64x160/1": 43.3, "128x64/1": 53.3}),
+    (128, 5120, 17408, RESID_F32, {"128x160/8": 44.4, "128x128/6": 47.0, "256x128/6": 49.6}),
+    (16, 4096, 12288, RESID_F32, {"16x64/4": 23.7, "rows": 27.2}),
+]
+
+
+@pytest.mark.parametrize("rows,width,depth,epi,times", MEASURED)
+def test_the_chosen_plan_is_near_the_fastest(check, rows, width, depth, epi, times):
+    out = subprocess.run([check, str(rows), str(width), str(depth), str(epi), str(1 << 28)], check=True,
+                         capture_output=True, text=True, timeout=60).stdout
+    kernel, _, slices, _ = out.strip().split("\n")[0].split("|")
+    tile = re.match(r"gemm_lds<(\d+), (\d+),", kernel)
+    plan = f"{tile[1]}x{tile[2]}/{slices}" if tile else "rows"
+    assert plan in times, plan
+    assert times[plan] <= 1.15 * min(times.values()), plan
