@@ -51,10 +51,11 @@ struct RopeParams {
   int num_cus;             // compute units of the device (sizes the grid)
   // nullable: the launch also writes the split attention's work items in
   // dispatch order (longest first) for splits of split_len tokens: every split
-  // that is not its sequence's last (split_len tokens each), by sequence and
-  // split; then each sequence's last split (split 0 of an empty sequence), by
-  // token count descending (to a 1024th of a split).  items holds batch * (splits of
-  // max_seq_len) pairs (sequence, split); *n_items receives the number written.
+  // that is not its sequence's last (split_len tokens each), by sequence, a
+  // sequence's rotated by its index; then each sequence's last split (split 0 of an
+  // empty sequence), by token count descending (to a 1024th of a split).  items holds
+  // batch * (splits of max_seq_len) pairs (sequence, split); *n_items receives the
+  // number written.
   int2* items;
   int* n_items;
   int split_len;

@@ -187,7 +187,11 @@ __device__ __forceinline__ void sincos_turns(double x, float& c, float& s) {
 // latency of their loads, four sequences per thread and pass where there are
 // that many.  Their time is proportional to the sequences: forwards of 1024, 4096
 // and 16384 sequences on a small head take 62, 184 and 635 us, and took 161, 1798
-// and 26392 when every pair of sequences was compared.
+// and 26392 when every pair of sequences was compared.  A sequence's full splits are
+// rotated by its index: in plain order, where their number shares a factor with the
+// XCDs, split j of every sequence lands on the same XCD, which then reads one offset of
+// every block at a time, and of contiguous blocks those lines lie on few memory
+// channels (44 sequences of 4782 tokens in nine splits, two KV heads: 107 us, 68).
 constexpr int kListBins = 1024;
 
 __device__ void write_work_list(const RopeParams& p, int batch, int* hist, int* wsum) {
@@ -236,8 +240,14 @@ __device__ void write_work_list(const RopeParams& p, int batch, int* hist, int* 
     }
     int total, at = full + scan(sum, total);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      for (int sp = 0; sp < nf[i]; ++sp) p.items[at++] = make_int2(b0 + per * tid + i, sp);
+    for (int i = 0; i < 4; ++i) {
+      const int b = b0 + per * tid + i;
+      int sp = nf[i] > 0 ? b % nf[i] : 0;  // rotated by the sequence (see above)
+      for (int j = 0; j < nf[i]; ++j) {
+        p.items[at++] = make_int2(b, sp);
+        if (++sp == nf[i]) sp = 0;
+      }
+    }
     full += total;
   }
   __syncthreads();
