@@ -18,6 +18,7 @@ import pytest
 
 from paper_2608_28099_amd import build_lib
 
+from . import test_gpu_gemm_stream as gemm_stream
 from . import test_gpu_reduce_norm as reduce_norm
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -72,7 +73,23 @@ def test_the_norm_runs_in_the_reduction(check, hidden, batch, intermediate, o, f
                 assert int(launches[0][2]) == slices, launches
 
 
-STORE, RESID_F32, SWIGLU = 0, 2, 3
+@pytest.mark.parametrize("intermediate,batch,tile", gemm_stream.CASES)
+def test_streaming_tiles_run_where_their_test_says(check, intermediate, batch, tile):
+    hidden, qw = gemm_stream.HIDDEN, gemm_stream.HEADS * gemm_stream.HEAD_DIM
+    part_bytes = 4 * max(16 * 32 * 2 * intermediate, 4 * batch * hidden)
+
+    def streaming(width, depth, epi):  # the tile that a product runs on, if a streaming one
+        out = subprocess.run([check, str(batch), str(width), str(depth), str(epi), str(part_bytes)], check=True,
+                             capture_output=True, text=True, timeout=60).stdout
+        m = re.match(r"gemm_lds<(\d+), (\d+), \d+, \d+, \d+, 64, true,", out)
+        return f"{m[1]}x{m[2]}" if m else None
+
+    assert streaming(2 * intermediate, hidden, SWIGLU) == tile
+    if batch > 16:  # o and down
+        assert streaming(hidden, qw, RESID_ROW) and streaming(hidden, intermediate, RESID_F32)
+
+
+STORE, RESID_ROW, RESID_F32, SWIGLU = 0, 1, 2, 3
 # rows, width, depth, epilogue; us of plans (tile / K slices, or the row kernel), fp16
 # image.  Off the heads the streaming tiles were tuned on, then on them
 MEASURED = [
