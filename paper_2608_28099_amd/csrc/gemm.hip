@@ -703,7 +703,7 @@ hipError_t launch_gemm_reduce(Epilogue epi, const GemmParams& p, int ksplit, int
 
 // K split ksplit ways (ksplit > 1: fp32 partials in p.part, then the reduction).
 // BM_WAVES x BN_WAVES: the waves of a workgroup for weights as stored.  Each wave
-// converts the columns it holds, so where BN_WAVES is 1 all WGM waves of a tile convert
+// converts the columns it holds, so where WGN is 1 all WGM waves of a tile would convert
 // all of its columns: 192 rows of 34816 x 5120 in 256 x 160 tiles took 491 us in 8 x 1
 // waves and 109 in 2 x 5 (fp16 image, 8 x 1: 112); 128 x 160, 128 rows of 24576 x 4096, 80.6 and
 // 58.2; 64 x 160, 58.7 and 46.0 on 33 rows; 128 x 96, 52.1 and 47.3.  The fp16 image is as
@@ -965,7 +965,7 @@ struct TilePlan { int tile, ksplit, first; };
 // The plan on the tiles that serve any number of rows.
 static TilePlan tile_plan(Epilogue epi, const GemmParams& p, int cus) {
   auto fits = [&](int ks) { return p.part && (size_t)ks * p.M * p.N * sizeof(float) <= p.part_bytes; };
-  // 17..32 rows of what the streaming tiles leave: a 32-row by 128-column tile
+  // 17..32 rows (where a streaming tile is not the cheaper plan): a 32-row by 128-column tile
   // with four waves, and K split so that the grid has enough workgroups in
   // flight (each slice at least 8 steps of 64).  (Up to 16 rows the one-wave
   // 16-row tiles below measured faster.)
@@ -990,8 +990,8 @@ static TilePlan tile_plan(Epilogue epi, const GemmParams& p, int cus) {
     const int ks = (int)std::min<long>(p.M > 256 && p.K >= 8192 ? 6 : 4, std::max<long>(2, cus / tiles));
     if (p.K % 64 == 0 && p.K / 64 >= 8 * ks && fits(ks)) return {2, ks, 0};
   }
-  // 33..256 rows of the other epilogues that the streaming tiles leave (QKV on more
-  // than 128 rows, K under 4096 there, narrow matrices): 128 x 64 tiles with K split
+  // 33..256 rows of the other epilogues (QKV on more than 128 rows, K under 4096 there,
+  // and where a streaming tile is not the cheaper plan): 128 x 64 tiles with K split
   // until the grid has a workgroup per compute unit (o on 256 rows of the 27B shape:
   // 58 us against 71 for 256 x 128).
   if (epi != kEpiSwiglu && p.M > 32 && p.M <= 256 && tile_ok(p, epi, kTiles[3]) && p.part) {

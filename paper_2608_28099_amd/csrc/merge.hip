@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void merge_splits(const MergeParams p) {
 // tile per workgroup, its SW waves each fold every SW-th split (wave 0 the soft
 // keys too), and the waves' (M, L, O) are combined through LDS in wave order.  A
 // single wave folds the splits one load round trip after another: one sequence of
-// 65536 tokens in 64 splits took 43.6 us, with eight waves 9 us.
+// 65536 tokens in 64 splits took 43.6 us, with eight waves 12.8 us (kernel trace).
 template <int HD, int SW>
 __global__ __launch_bounds__(SW == 1 ? 256 : 64 * SW) void merge_soft_mfma(const MergeParams p) {
   constexpr int NC = HD / 32, NDT = HD / 16;

@@ -215,8 +215,8 @@ AttnPlan attn_plan(const sp_probe_config& c, int rows, int num_cus, bool coarse)
     const int64_t third = ((int64_t)c.max_seq_len + 2) / 3;
     const int64_t sl = (std::min(want, third) + 255) / 256 * 256;
     a.split_len = (int)std::max<int64_t>(sl, kCoarseSplit);
-    // A batch too small to fill the round in splits of 1024 tokens takes the
-    // length that fills it, at least 256: 2048 tokens of one sequence over 8 KV
+    // A handle whose max_batch is too small to fill the round in splits of 1024 tokens
+    // (whatever a call's batch) takes the length that fills it, at least 256: 2048 tokens of one sequence over 8 KV
     // heads in eight splits of 256 (forward 125 us, 147 in two of 1024), nine
     // ragged sequences of up to 3000 in ten splits of 320 (recursive SP-2 287 us
     // against 321).  A single sequence has no raggedness to balance and fills two
@@ -229,9 +229,10 @@ AttnPlan attn_plan(const sp_probe_config& c, int rows, int num_cus, bool coarse)
       a.split_len = (int)std::max<int64_t>((len + 63) / 64 * 64, kFineSplit);
     }
   } else {
-    // fp32 path: at most 8 splits per sequence, between 1024 and 16384 tokens
-    // each; shorter ones (256 tokens or more) where a small batch leaves compute
-    // units without a workgroup.
+    // fp32 path: splits of 1024 tokens, longer ones (up to 16384) where a sequence
+    // would have more than 8; but shorter ones (256 tokens or more, and then as many as
+    // there are: one sequence of 131072 tokens over 2 KV heads in 128) where a small
+    // max_batch leaves compute units without a workgroup.
     int sl = 1024;
     while (sl < 16384 && (int64_t)sl * 8 < c.max_seq_len) sl *= 2;
     const int64_t items = (int64_t)c.max_batch * c.n_kv_heads * tiles;
@@ -334,8 +335,9 @@ Plan make_plan(const sp_probe_config& c, int num_cus, bool coarse) {
   return p;
 }
 
-// The plan of a handle, and of the call without one: short splits where they pay,
-// unless only the coarse plan's smaller workspace fits the static scratch.
+// The plan of a handle, and of the call without one (the same, so that their results
+// are): short splits where they pay, unless only the coarse plan's smaller workspace
+// fits the static scratch; a config whose coarse plan does not fit either keeps them.
 Plan make_plan(const sp_probe_config& c, int num_cus) {
   const Plan fine = make_plan(c, num_cus, false);
   if (fine.total <= kScratchBytes) return fine;
